@@ -93,12 +93,19 @@ __global__ __launch_bounds__(kBlock) void k_ubar_init(GradArgs a) {
   }
 }
 
-// w = L v_j (periodic 7-point Laplacian)
+// w = L v_j (periodic 7-point Laplacian), and the largest |v_j| of any component,
+// which bounds the splat's reach.  This pass reads v_j anyway, so the maximum
+// costs no traffic: a pass of its own over v_j by one block took 2553 us at
+// 128^3 (10 GB/s) and was 92 % of the whole gradient's time.  A block adds to the
+// maximum only when its own is larger than what it reads there, so nearly all
+// of the 8192 blocks leave the address alone; a maximum has no order, so the
+// result is the same.  NaN components are passed over, as fmaxf does.
 __global__ __launch_bounds__(kBlock) void k_Lv(GradArgs a) {
   const Geom g = a.g;
   const long long N = g.n;
   const uint32_t n = (uint32_t)N;
   const float c2 = a.alpha * g.inv_h * g.inv_h;
+  float m = 0.f;
   for (int c = 0; c < 3; ++c) {
     const rsrc_t V = rsrc(a.v + c * N, n), W = rsrc(a.w + c * N, n);
     for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
@@ -106,9 +113,28 @@ __global__ __launch_bounds__(kBlock) void k_Lv(GradArgs a) {
       vcoord(g, i, x, y, z);
       const Nbr nb = periodic_nbr(g, i, x, y, z);
       const float v0 = bld(V, i);
+      m = fmaxf(m, fabsf(v0));
       bst(W, i, a.gamma * v0 - c2 * lap7_b(V, nb, v0));
     }
   }
+  __shared__ float red[kBlock / 64];
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_down(m, off, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int k = 1; k < kBlock / 64; ++k) m = fmaxf(m, red[k]);
+    // non-negative floats order as their bits do
+    const int bits = __builtin_bit_cast(int, m);
+    if (bits > __hip_atomic_load(a.vmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(a.vmax, bits);
+  }
+}
+
+// Splat radius: floor(max_x max_axis |dt v_j / h|) + 1 (at least one source
+// further than any displacement reaches).
+__device__ __forceinline__ int splat_radius(const GradArgs& a) {
+  const float d = __builtin_bit_cast(float, *a.vmax) * (a.dt * a.g.inv_h);
+  return (int)floorf(fminf(d, 1e6f)) + 1;
 }
 
 // dE/dv_j = -dt ubar - (dt/h) (d_y S_clamp(u_j; y_j))^T ubar + reg * L w
@@ -156,7 +182,7 @@ __global__ __launch_bounds__(kBlock) void k_splat(GradArgs a) {
   const rsrc_t V0 = rsrc(a.v, n), V1 = rsrc(a.v + N, n), V2 = rsrc(a.v + 2 * N, n);
   const rsrc_t B0 = rsrc(a.ub_in, n), B1 = rsrc(a.ub_in + N, n), B2 = rsrc(a.ub_in + 2 * N, n);
   const rsrc_t O0 = rsrc(a.ub_out, n), O1 = rsrc(a.ub_out + N, n), O2 = rsrc(a.ub_out + 2 * N, n);
-  int Rr = *a.radius;
+  int Rr = splat_radius(a);
   if (Rr > kSplatMaxR) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.overflow = 1;
     Rr = kSplatMaxR;
@@ -196,24 +222,6 @@ __global__ __launch_bounds__(kBlock) void k_splat(GradArgs a) {
   }
 }
 
-// Splat radius of step j: Rr = floor(max_x max_axis |dt v_j / h|) + 1, as a device int.
-__global__ __launch_bounds__(1024) void k_radius(const float* v, long long N, float scale,
-                                                 int* radius) {
-  __shared__ float red[1024];
-  float m = 0.f;
-  for (long long i = threadIdx.x; i < 3 * N; i += blockDim.x) m = fmaxf(m, fabsf(v[i]));
-  red[threadIdx.x] = m;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + s]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const float d = red[0] * scale;
-    *radius = (d == d) ? (int)floorf(fminf(d, 1e6f)) + 1 : kSplatMaxR + 1;
-  }
-}
-
 // ------------------------------------------------------------ launchers
 
 void launch_ubar_init(const GradArgs& a, hipStream_t s) {
@@ -225,8 +233,6 @@ void launch_ubar_init(const GradArgs& a, hipStream_t s) {
 
 void launch_grad_step(const GradArgs& a, hipStream_t s) {
   const unsigned gb = grid_for(a.g.n);
-  hipLaunchKernelGGL(k_radius, dim3(1), dim3(1024), 0, s, a.v, a.g.n, a.dt * a.g.inv_h,
-                     (int*)a.radius);
   hipLaunchKernelGGL(k_Lv, dim3(gb), dim3(kBlock), 0, s, a);
   hipLaunchKernelGGL(k_coord_grad, dim3(gb), dim3(kBlock), 0, s, a);
   hipLaunchKernelGGL(k_splat, dim3(gb), dim3(kBlock), 0, s, a);

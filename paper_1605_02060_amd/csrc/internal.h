@@ -285,7 +285,7 @@ struct GradArgs {
   float* w;              // L v_j scratch [3][n]
   float* grad;           // dE/dv_j [3][n]
   float dt, alpha, gamma, reg;   // reg = 2 dt h^3
-  const int* radius;     // device: splat radius for this step
+  int* vmax;             // device: bits of max |v_j|, zero before the step (sets the splat's reach)
   int* overflow;         // device flag: radius beyond the supported maximum
 };
 void launch_ubar_init(const GradArgs& a, hipStream_t s);
