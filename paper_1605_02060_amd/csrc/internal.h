@@ -285,7 +285,9 @@ struct GradArgs {
   float* w;              // L v_j scratch [3][n]
   float* grad;           // dE/dv_j [3][n]
   float dt, alpha, gamma, reg;   // reg = 2 dt h^3
-  int* vmax;             // device: bits of max |v_j|, zero before the step (sets the splat's reach)
+  float* vpart;          // device: max |v_j| per block of the L v pass, nvpart of them
+  int nvpart;
+  float* vmax;           // device: max |v_j| of the step (sets the splat's reach)
   int* overflow;         // device flag: radius beyond the supported maximum
 };
 void launch_ubar_init(const GradArgs& a, hipStream_t s);

@@ -659,9 +659,10 @@ static void exact_gradient(Ctx& c, const float* v, float* grad, hipStream_t s) {
   a.gamma = (float)c.gamma;
   a.reg = (float)(2.0 / T * h * h * h);
   a.w = c.b;
-  // one maximum per step, in the min-det partials, which this path does not use
-  int* const vmax = (int*)c.partDet;
-  launch_fill((float*)vmax, T, 0.f, s);
+  // the velocity's maxima in buffers that this path does not use: per block in the min-det
+  // partials, the step's in misc
+  a.vpart = (float*)c.partDet;
+  a.vmax = (float*)c.misc;
   a.overflow = c.misc + 1;
   a.u = c.u0 + (long long)sl[T] * 3 * n;
   a.ub_out = c.ub + (long long)(T & 1) * 3 * n;
@@ -685,7 +686,6 @@ static void exact_gradient(Ctx& c, const float* v, float* grad, hipStream_t s) {
     }
     a.u = c.u0 + (long long)uslot * 3 * n;
     a.v = v + (long long)j * 3 * n;
-    a.vmax = vmax + j;
     a.ub_in = c.ub + (long long)((j + 1) & 1) * 3 * n;
     a.ub_out = c.ub + (long long)(j & 1) * 3 * n;
     a.grad = grad + (long long)j * 3 * n;
@@ -1238,7 +1238,7 @@ static int gradient_call(const lddmm_problem* p, const lddmm_params* prm, int32_
   setup_images(c, p, s);
   launch_level_begin(c.st, 1.0, 0, s);
   if (kind == LDDMM_GRAD_L2) {
-    launch_fill((float*)c.misc, 2, 0.f, s);   // overflow flag in [1] (zero bits)
+    launch_fill((float*)c.misc, 2, 0.f, s);   // max |v_j|, overflow flag (zero bits)
     exact_gradient(c, p->v, grad, s);
     launch_energy_out_checked(c.st, c.misc + 1, out4, s);
     return hip_status();
