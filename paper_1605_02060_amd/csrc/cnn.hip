@@ -2,37 +2,17 @@
 // gradient, weight gradient) as implicit GEMMs on the bf16 matrix cores, and
 // the small elementwise layers around them.  Activations and weights are bf16
 // in HBM, every sum accumulates in FP32 (MFMA) or FP64 (losses).
-#include <hip/hip_runtime.h>
-#include <stdint.h>
-
 #include <algorithm>
 #include <cmath>
 
-#include "lddmm_cnn.h"
+#include "cnn_internal.h"
 
 namespace lddmm_cnn {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint16_t u16;
 
 constexpr int kThreads = 256;     // 4 wavefronts of 64
 constexpr int BK = 32;            // K per MFMA step (v_mfma_f32_16x16x32_bf16)
 constexpr int LDK = BK + 8;       // LDS row stride in bf16: 80 bytes, 16-byte aligned rows
 
-__device__ __forceinline__ float bf2f(u16 b) {
-  return __builtin_bit_cast(float, (uint32_t)b << 16);
-}
-
-// Round to nearest bf16, ties to even (NaN stays NaN).
-__device__ __forceinline__ u16 f2bf(float f) {
-  uint32_t u = __builtin_bit_cast(uint32_t, f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (u16)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (u16)(u >> 16);
-}
-
-enum { OP_FWD = 0, OP_DGRAD = 1, OP_WGRAD = 2 };
 
 // One convolution as C[M x N] = sum_k A[m][k] B[k][n]:
 //  forward : m = output voxel, n = output channel, k = (tap, input channel);
@@ -43,20 +23,6 @@ enum { OP_FWD = 0, OP_DGRAD = 1, OP_WGRAD = 2 };
 //  wgrad   : m = output channel, n = (tap, input channel), k = output voxel;
 //            A = dy[k][m], B = input at s*k + tap - 1; the K range is split
 //            over blockIdx.z and the partial tiles are reduced afterwards.
-struct ConvArgs {
-  const u16* x;       // forward / wgrad input; dgrad: dy
-  const u16* wb;      // forward: w; dgrad: wt; wgrad: dy
-  const float* bias;
-  const u16* mask;
-  const u16* add;
-  void* out;          // forward: y; dgrad: dx; wgrad: FP32 partial tiles
-  int n, d, h, w, ci; // input geometry
-  int od, oh, ow, co; // output geometry
-  int s;
-  int M, N, K, kchunk;
-  int relu, out_f32, add_stride, add_off;
-};
-
 // (b, z, y, x) of voxel index m on an n x d x h x w grid, as (b d + z, y, x).
 __device__ __forceinline__ void split_voxel(int m, int d, int h, int w, int& bz, int& y, int& x) {
   x = m % w;
@@ -642,7 +608,8 @@ int lddmm_conv3d_forward(const uint16_t* x, lddmm_cnn_shape xs, const uint16_t* 
   a.kchunk = a.K;
   hipGetLastError();
   const bool vec = (xs.c % 8) == 0;
-  launch_mk<OP_FWD>(a, vec, vec, (hipStream_t)stream);
+  if (!launch_conv_frag(OP_FWD, a, (hipStream_t)stream))
+    launch_mk<OP_FWD>(a, vec, vec, (hipStream_t)stream);
   return hip_ok();
 }
 
@@ -673,7 +640,8 @@ int lddmm_conv3d_backward_data(const uint16_t* dy, lddmm_cnn_shape xs, int32_t c
   a.kchunk = a.K;
   hipGetLastError();
   const bool vec = (cout % 8) == 0;
-  launch_mk<OP_DGRAD>(a, vec, vec, (hipStream_t)stream);
+  if (!launch_conv_frag(OP_DGRAD, a, (hipStream_t)stream))
+    launch_mk<OP_DGRAD>(a, vec, vec, (hipStream_t)stream);
   return hip_ok();
 }
 
