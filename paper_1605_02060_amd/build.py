@@ -19,7 +19,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "liblddmm.so")
 
 SOURCES = ["flow.hip", "fft.hip", "control.hip", "grad.hip", "runtime.hip", "cnn.hip", "conv.hip",
-           "hist.hip", "align.hip", "masks.hip"]
+           "wgrad.hip", "hist.hip", "align.hip", "masks.hip"]
 ARCH = "gfx950"
 
 

@@ -680,6 +680,9 @@ int lddmm_conv3d_backward_weight(const uint16_t* dy, const uint16_t* x, lddmm_cn
   a.kchunk = kchunk;
   hipStream_t s = (hipStream_t)stream;
   hipGetLastError();
+  // scratch as required, not as given: the splits, and so the sums' order, depend on it
+  if (launch_wgrad(a, dw, db, part, lddmm_conv3d_wgrad_workspace(xs, cout, stride) / sizeof(float), s))
+    return hip_ok();
   const bool va = (cout % 8) == 0, vb = (xs.c % 8) == 0;
   const dim3 grid((cout + wgrad_bm(cout) - 1) / wgrad_bm(cout), (a.N + 63) / 64, nsplit);
   if (cout <= 16)

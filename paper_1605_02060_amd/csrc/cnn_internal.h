@@ -47,4 +47,9 @@ struct ConvArgs {
 // does not cover.
 bool launch_conv_frag(int op, const ConvArgs& a, hipStream_t s);
 
+// wgrad.hip: weight and bias (db may be null) gradients with part_floats floats of scratch.
+// Returns false, launching nothing, for shapes it does not cover.
+bool launch_wgrad(const ConvArgs& a, float* dw, float* db, float* part, size_t part_floats,
+                  hipStream_t s);
+
 }  // namespace lddmm_cnn

@@ -54,3 +54,26 @@ def test_backward_data(n, dims, ci, co, stride):
     lim = bound(27 * co, C.conv3d_dgrad(np.abs(dq), np.abs(wq), shp, stride)
                 + np.abs(aq[..., 2:2 + ci]))
     assert np.all(np.abs(dx - ref) <= lim)
+
+
+@pytest.mark.parametrize("n,dims,ci,co,stride", [
+    (1, (1, 1, 1), 16, 16, 1), (1, (2, 8, 8), 16, 32, 1), (2, (3, 9, 7), 16, 40, 2),
+    (1, (5, 17, 16), 16, 30, 2), (1, (4, 7, 9), 32, 17, 1), (1, (5, 15, 18), 32, 64, 2),
+    (2, (3, 8, 9), 64, 30, 1), (1, (3, 5, 8), 48, 33, 2), (1, (4, 9, 8), 96, 70, 1),
+    (1, (1, 1, 1), 2, 16, 1), (2, (5, 9, 17), 2, 16, 1), (1, (3, 8, 10), 2, 9, 1),
+    (1, (4, 6, 7), 2, 40, 1),
+])
+def test_backward_weight(n, dims, ci, co, stride):
+    print(f"[gpu-case] conv wgrad {n} {dims} {ci}->{co} s={stride}", flush=True)
+    rng = np.random.default_rng(7)
+    xq, xg = bf(rng.normal(size=(n,) + dims + (ci,)))
+    dq, dg = bf(rng.normal(size=(n,) + tuple(C.out_size(v, stride) for v in dims) + (co,)))
+    dw, db = G.conv3d_backward_weight(dg, xg, stride)
+    ref_w, ref_b = C.conv3d_wgrad(dq, xq, stride)
+    abs_w, abs_b = C.conv3d_wgrad(np.abs(dq), np.abs(xq), stride)
+    K = int(np.prod(dq.shape[:4]))          # as test_gpu_cnn: the K-term sequential bound
+    assert np.all(np.abs(host(dw) - ref_w) <= bound(K + 1024, abs_w))
+    assert np.all(np.abs(host(db) - ref_b) <= bound(K + 1024, abs_b))
+    only = torch.empty_like(dw)
+    again, _ = G.conv3d_backward_weight(dg, xg, stride, dw=only)
+    assert torch.equal(again, dw)           # deterministic
