@@ -5,11 +5,11 @@
 
 namespace lddmm {
 
-__global__ void k_level_begin(State* st, double step, int keep_flags) {
+__global__ void k_level_begin(State* st, double step, int keep_flags, int base) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   st->mode = (keep_flags && st->nonfinite) ? MODE_STOPPED : MODE_INIT;
-  st->base = 0;
-  st->eval = 0;
+  st->base = base == kOtherBase ? 1 - st->base : base;
+  st->eval = st->base;
   st->halvings = 0;
   if (!keep_flags) {
     st->row = 0;
@@ -22,8 +22,8 @@ __global__ void k_level_begin(State* st, double step, int keep_flags) {
   st->min_det = __longlong_as_double(0x7ff8000000000000LL);   // NaN until a gradient is taken
 }
 
-void launch_level_begin(State* st, double step, int keep_flags, hipStream_t s) {
-  hipLaunchKernelGGL(k_level_begin, dim3(1), dim3(64), 0, s, st, step, keep_flags);
+void launch_level_begin(State* st, double step, int keep_flags, int base, hipStream_t s) {
+  hipLaunchKernelGGL(k_level_begin, dim3(1), dim3(64), 0, s, st, step, keep_flags, base);
 }
 
 // Three sums over one 1024-thread block at once (per-thread values in, totals out

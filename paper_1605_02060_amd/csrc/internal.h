@@ -226,6 +226,9 @@ void launch_down2(const float* src, const Geom& fine, float* dst, const Geom& co
                   int nfields, hipStream_t s);
 void launch_up2(const float* src, const Geom& coarse, float* dst, const Geom& fine, int nfields,
                 hipStream_t s);
+// The same from the iterate's buffer (vA or vB, by st->base) to the other one.
+void launch_up2_iterate(float* vA, float* vB, const State* st, const Geom& coarse, const Geom& fine,
+                        int nfields, hipStream_t s);
 int reduce_grid(long long n);
 void set_sweep_blocks(int blocks);
 void set_fft_x_elems(int elems);
@@ -254,6 +257,8 @@ void launch_make_mask(const float* img, long long n, float tau, float* m, float*
                       hipStream_t s);
 void launch_fill(float* p, long long n, float val, hipStream_t s);
 void launch_copy(const float* src, float* dst, long long n, hipStream_t s);
+void launch_copy_iterate(const float* vA, const float* vB, const State* st, float* dst, long long n,
+                         hipStream_t s);
 
 // fft.hip
 bool make_plan(int n, FFTPlan* p);
@@ -295,7 +300,9 @@ void launch_grad_step(const GradArgs& a, hipStream_t s);
 
 // control.hip
 void launch_energy_out_checked(const State* st, const int* overflow, double* out4, hipStream_t s);
-void launch_level_begin(State* st, double step, int keep_flags, hipStream_t s);
+// base: the buffer that holds the level's first iterate; kOtherBase: the one that did not so far.
+constexpr int kOtherBase = -1;
+void launch_level_begin(State* st, double step, int keep_flags, int base, hipStream_t s);
 void launch_decide(State* st, const double* partR, int T, const double* partD,
                    const double* partI, const double* partDet, int nblk_fwd, int nblk_bwd,
                    int has_img, double dt, double h3, double inv_sigma2, int guard,

@@ -605,18 +605,18 @@ static void backward_sweep(Ctx& c, int li, float* vA, float* vB, const float* vf
 
 static void decide(Ctx& c, int li, int init, double* trace, hipStream_t s);
 
-// Outputs of the final iterate (buffer 0) at the finest level: phi_10 (if asked),
+// Outputs of the final iterate v at the finest level: phi_10 (if asked),
 // phi_01 (if asked) and the min det of its maps phi_{t_j,1}, which decides
 // LDDMM_WFOLD.  The forward sweep gives the deformed templates and the residual
 // the body-force steps read; the body forces themselves are discarded.
-static void final_outputs(Ctx& c, float* phi10, float* phi01, hipStream_t s) {
+static void final_outputs(Ctx& c, float* v, float* phi10, float* phi01, hipStream_t s) {
   const Config& k = c.cfg;
   const int top = k.L - 1;
   const Level& L = k.lv[top];
-  forward_sweep(c, top, c.v[0], c.v[1], false, s);
+  forward_sweep(c, top, v, v, false, s);
   if (phi10)
     launch_crop3(u0_final(c, top, false), L.g, L.N[0], L.N[1], L.N[2], phi10, s);
-  backward_sweep(c, top, c.v[0], c.v[1], c.v[0], true, UPD_STEP, nullptr, -1, s, false);
+  backward_sweep(c, top, v, v, v, true, UPD_STEP, nullptr, -1, s, false);
   launch_final_det(c.st, c.partDet, k.T, backward_partials(L.g), s);
   if (phi01) launch_crop3(c.u1, L.g, L.N[0], L.N[1], L.N[2], phi01, s);
 }
@@ -703,27 +703,27 @@ static void decide(Ctx& c, int li, int init, double* trace, hipStream_t s) {
                 1.0 / c.cfg.T, h * h * h, 1.0 / (c.sigma * c.sigma), c.guard, trace, init, s);
 }
 
-// Copy the current iterate into buffer 0 (kernel reads st->base).
-__global__ void k_canon(float* v0, const float* v1, long long count, const State* st) {
-  if (st->base == 0) return;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < count;
-       i += (long long)gridDim.x * blockDim.x)
-    v0[i] = v1[i];
+__global__ void k_set_mode(State* st, int mode) {
+  if (threadIdx.x == 0) st->mode = mode;
 }
 
-__global__ void k_set_base(State* st, int base, int mode) {
-  if (threadIdx.x == 0) {
-    st->base = base;
-    st->eval = base;
-    if (mode >= 0) st->mode = mode;
+// Initial velocity at the coarsest level: the finest one block-averaged down (copied with one
+// level).  Returns the buffer that holds it.
+static int initial_velocity(Ctx& c, const float* v, hipStream_t s) {
+  const Config& k = c.cfg;
+  const int top = k.L - 1;
+  if (top == 0) {
+    launch_copy(v, c.v[0], 3 * k.lv[0].g.n * k.T, s);
+    return 0;
   }
-}
-
-static void canonicalize(Ctx& c, long long count, hipStream_t s) {
-  long long b = (count + 255) / 256;
-  if (b > 65536) b = 65536;
-  hipLaunchKernelGGL(k_canon, dim3((unsigned)b), dim3(256), 0, s, c.v[0], c.v[1], count, c.st);
-  hipLaunchKernelGGL(k_set_base, dim3(1), dim3(64), 0, s, c.st, 0, -1);
+  const float* src = v;
+  int dst = 1;
+  for (int li = top - 1; li >= 0; --li) {
+    launch_down2(src, k.lv[li + 1].g, c.v[dst], k.lv[li].g, 3 * k.T, s);
+    src = c.v[dst];
+    dst ^= 1;
+  }
+  return dst ^ 1;
 }
 
 static void setup_images(Ctx& c, const lddmm_problem* p, hipStream_t s) {
@@ -852,26 +852,13 @@ int lddmm_register(lddmm_problem* p, int32_t n_problems, const lddmm_params* prm
   double* trace = p->trace ? p->trace : c.trace;
 
   setup_images(c, p, s);
-  // initial velocity at the coarsest level: block-average the finest one down
-  {
-    const float* src = p->v;
-    int dst = 1;
-    for (int li = top - 1; li >= 0; --li) {
-      launch_down2(src, k.lv[li + 1].g, c.v[dst], k.lv[li].g, 3 * k.T, s);
-      src = c.v[dst];
-      dst ^= 1;
-    }
-    launch_copy(src, c.v[0], 3 * k.lv[0].g.n * k.T, s);
-  }
-  launch_level_begin(c.st, prm->step, 0, s);
+  launch_level_begin(c.st, prm->step, 0, initial_velocity(c, p->v, s), s);
   for (int li = 0; li <= top; ++li) {
     const Level& L = k.lv[li];
     if (li > 0) {
-      // iterate of the previous level -> buffer 0, upsample into buffer 1
-      canonicalize(c, 3 * k.lv[li - 1].g.n * k.T, s);
-      launch_up2(c.v[0], k.lv[li - 1].g, c.v[1], L.g, 3 * k.T, s);
-      launch_copy(c.v[1], c.v[0], 3 * L.g.n * k.T, s);
-      launch_level_begin(c.st, prm->step, 1, s);
+      // iterate of the previous level, upsampled into the other buffer
+      launch_up2_iterate(c.v[0], c.v[1], c.st, k.lv[li - 1].g, L.g, 3 * k.T, s);
+      launch_level_begin(c.st, prm->step, 1, kOtherBase, s);
     }
     level_tables(c, L, s);
     forward_sweep(c, li, c.v[0], c.v[1], false, s);
@@ -888,10 +875,9 @@ int lddmm_register(lddmm_problem* p, int32_t n_problems, const lddmm_params* prm
     }
   }
   // outputs from the final iterate
-  canonicalize(c, 3 * nf * k.T, s);
-  launch_copy(c.v[0], p->v, 3 * nf * k.T, s);
-  hipLaunchKernelGGL(k_set_base, dim3(1), dim3(64), 0, s, c.st, 0, (int)MODE_INIT);
-  final_outputs(c, p->phi10, p->phi01, s);
+  launch_copy_iterate(c.v[0], c.v[1], c.st, p->v, 3 * nf * k.T, s);
+  hipLaunchKernelGGL(k_set_mode, dim3(1), dim3(64), 0, s, c.st, (int)MODE_INIT);
+  final_outputs(c, p->v, p->phi10, p->phi01, s);
   rc = hip_status();
   if (rc) return rc;
   State hs{};
@@ -1060,15 +1046,7 @@ extern "C" int lddmm_register_batched(lddmm_problem* probs, int32_t n, const ldd
     const Config& k = c.cfg;
     const int top = k.L - 1;
     setup_images(c, &probs[p], s);
-    const float* src = probs[p].v;
-    int dst = 1;
-    for (int li = top - 1; li >= 0; --li) {
-      launch_down2(src, k.lv[li + 1].g, c.v[dst], k.lv[li].g, 3 * k.T, s);
-      src = c.v[dst];
-      dst ^= 1;
-    }
-    launch_copy(src, c.v[0], 3 * k.lv[0].g.n * k.T, s);
-    launch_level_begin(c.st, prm->step, 0, s);
+    launch_level_begin(c.st, prm->step, 0, initial_velocity(c, probs[p].v, s), s);
   }
   std::vector<PairTab*> dtabs(n);
   for (int p = 0; p < n; ++p) dtabs[p] = cs[p].ptab;
@@ -1080,10 +1058,8 @@ extern "C" int lddmm_register_batched(lddmm_problem* probs, int32_t n, const ldd
       const Config& k = c.cfg;
       const Level& lv = k.lv[li];
       if (li > 0) {
-        canonicalize(c, 3 * k.lv[li - 1].g.n * k.T, s);
-        launch_up2(c.v[0], k.lv[li - 1].g, c.v[1], lv.g, 3 * k.T, s);
-        launch_copy(c.v[1], c.v[0], 3 * lv.g.n * k.T, s);
-        launch_level_begin(c.st, prm->step, 1, s);
+        launch_up2_iterate(c.v[0], c.v[1], c.st, k.lv[li - 1].g, lv.g, 3 * k.T, s);
+        launch_level_begin(c.st, prm->step, 1, kOtherBase, s);
       }
       level_tables(c, lv, s);
       PairTab* ht = &host_tabs[(size_t)li * n + p];
@@ -1144,10 +1120,9 @@ extern "C" int lddmm_register_batched(lddmm_problem* probs, int32_t n, const ldd
     const int top = k.L - 1;
     const long long nf = k.lv[top].g.n;
     lddmm_problem* pr = &probs[p];
-    canonicalize(c, 3 * nf * k.T, s);
-    launch_copy(c.v[0], pr->v, 3 * nf * k.T, s);
-    hipLaunchKernelGGL(k_set_base, dim3(1), dim3(64), 0, s, c.st, 0, (int)MODE_INIT);
-    final_outputs(c, pr->phi10, pr->phi01, s);
+    launch_copy_iterate(c.v[0], c.v[1], c.st, pr->v, 3 * nf * k.T, s);
+    hipLaunchKernelGGL(k_set_mode, dim3(1), dim3(64), 0, s, c.st, (int)MODE_INIT);
+    final_outputs(c, pr->v, pr->phi10, pr->phi01, s);
     if (pr->trace) {
       const int rows = trace_rows(prm);
       hipMemcpyAsync(pr->trace, c.trace, sizeof(double) * 8 * rows, hipMemcpyDeviceToDevice, s);
@@ -1192,7 +1167,7 @@ int lddmm_energy(const lddmm_problem* p, const lddmm_params* prm, double* out4, 
   hipStream_t s = (hipStream_t)stream;
   hipGetLastError();
   setup_images(c, p, s);
-  launch_level_begin(c.st, 1.0, 0, s);
+  launch_level_begin(c.st, 1.0, 0, 0, s);
   level_tables(c, c.cfg.lv[0], s);
   forward_sweep(c, 0, p->v, p->v, false, s);
   decide(c, 0, 1, c.trace, s);
@@ -1236,7 +1211,7 @@ static int gradient_call(const lddmm_problem* p, const lddmm_params* prm, int32_
   hipStream_t s = (hipStream_t)stream;
   hipGetLastError();
   setup_images(c, p, s);
-  launch_level_begin(c.st, 1.0, 0, s);
+  launch_level_begin(c.st, 1.0, 0, 0, s);
   if (kind == LDDMM_GRAD_L2) {
     launch_fill((float*)c.misc, 2, 0.f, s);   // max |v_j|, overflow flag (zero bits)
     exact_gradient(c, p->v, grad, s);
@@ -1313,7 +1288,7 @@ int lddmm_smooth(const int32_t P[3], double spacing, double alpha, double gamma,
   c.S = (float2*)(w + off);
   c.alpha = alpha;
   c.gamma = gamma;
-  launch_level_begin(c.st, 1.0, 0, s);
+  launch_level_begin(c.st, 1.0, 0, 0, s);
   level_tables(c, L, s);
   launch_copy(b, c.b, 3 * L.g.n, s);
   UpdArgs u{};
