@@ -210,27 +210,43 @@ __device__ __forceinline__ float tri_clamped(const float* __restrict__ f, const 
                f[o + sz + sy + 1], fx, fy, fz);
 }
 
-// Trilinear sample with zero outside the grid.
+// f[o] and f[o + 1] in one load, 4-byte aligned; a row of one voxel has no second.
+struct __attribute__((packed, aligned(4))) FloatPair {
+  float a, b;
+};
+
+template <bool PAIR>
+__device__ __forceinline__ FloatPair load_pair(const float* __restrict__ f, uint32_t o) {
+  if (PAIR) return *reinterpret_cast<const FloatPair*>(f + o);
+  const float v = f[o];
+  return FloatPair{v, v};
+}
+
+// Trilinear sample with zero outside the grid; PAIR: rows of at least two voxels.
+template <bool PAIR>
 __device__ __forceinline__ float tri_zero(const float* __restrict__ f, const Geom& g, int cx, int cy,
                                           int cz, float fx, float fy, float fz) {
   const bool x0 = (unsigned)cx < (unsigned)g.nx, x1 = (unsigned)(cx + 1) < (unsigned)g.nx;
   const bool y0 = (unsigned)cy < (unsigned)g.ny, y1 = (unsigned)(cy + 1) < (unsigned)g.ny;
   const bool z0 = (unsigned)cz < (unsigned)g.nz, z1 = (unsigned)(cz + 1) < (unsigned)g.nz;
-  if (!((x0 || x1) && (y0 || y1) && (z0 || z1))) return 0.f;
-  const int ax = x0 ? cx : cx + 1, bx = x1 ? cx + 1 : cx;
-  const int ay = y0 ? cy : cy + 1, by = y1 ? cy + 1 : cy;
-  const int az = z0 ? cz : cz + 1, bz = z1 ? cz + 1 : cz;
+  // every corner is loaded, those outside the grid from the nearest voxel inside, and
+  // zeroed after (a branch around each load cost more than the loads); the two corners along
+  // x in one load of 8 bytes: a gather costs the cache as much for 8 bytes a lane as for 4
+  const int px = max(min(cx, g.nx - 2), 0);
+  const int ay = min(max(cy, 0), g.ny - 1), az = min(max(cz, 0), g.nz - 1);
   const uint32_t sy = (uint32_t)g.nx, sz = (uint32_t)(g.nx * g.ny);
-  const uint32_t ya = ay * sy, yb = by * sy, za = az * sz, zb = bz * sz;
-  auto ld = [&](bool ok, uint32_t off) { return ok ? f[off] : 0.f; };
-  const float v000 = ld(x0 && y0 && z0, za + ya + ax);
-  const float v100 = ld(x1 && y0 && z0, za + ya + bx);
-  const float v010 = ld(x0 && y1 && z0, za + yb + ax);
-  const float v110 = ld(x1 && y1 && z0, za + yb + bx);
-  const float v001 = ld(x0 && y0 && z1, zb + ya + ax);
-  const float v101 = ld(x1 && y0 && z1, zb + ya + bx);
-  const float v011 = ld(x0 && y1 && z1, zb + yb + ax);
-  const float v111 = ld(x1 && y1 && z1, zb + yb + bx);
+  const uint32_t r00 = (uint32_t)az * sz + (uint32_t)ay * sy + (uint32_t)px;
+  const uint32_t r10 = r00 + (y0 && y1 ? sy : 0u), dz = z0 && z1 ? sz : 0u;
+  const FloatPair p00 = load_pair<PAIR>(f, r00), p10 = load_pair<PAIR>(f, r10);
+  const FloatPair p01 = load_pair<PAIR>(f, r00 + dz), p11 = load_pair<PAIR>(f, r10 + dz);
+  const float t000 = cx > px ? p00.b : p00.a, t100 = cx < px ? p00.a : p00.b;
+  const float t010 = cx > px ? p10.b : p10.a, t110 = cx < px ? p10.a : p10.b;
+  const float t001 = cx > px ? p01.b : p01.a, t101 = cx < px ? p01.a : p01.b;
+  const float t011 = cx > px ? p11.b : p11.a, t111 = cx < px ? p11.a : p11.b;
+  const float v000 = x0 && y0 && z0 ? t000 : 0.f, v100 = x1 && y0 && z0 ? t100 : 0.f;
+  const float v010 = x0 && y1 && z0 ? t010 : 0.f, v110 = x1 && y1 && z0 ? t110 : 0.f;
+  const float v001 = x0 && y0 && z1 ? t001 : 0.f, v101 = x1 && y0 && z1 ? t101 : 0.f;
+  const float v011 = x0 && y1 && z1 ? t011 : 0.f, v111 = x1 && y1 && z1 ? t111 : 0.f;
   return lerp8(v000, v100, v010, v110, v001, v101, v011, v111, fx, fy, fz);
 }
 

@@ -1349,36 +1349,61 @@ void launch_crop3(const float* u, const Geom& g, int Nx, int Ny, int Nz, float* 
                      Nz, out);
 }
 
-template <typename TS>
+// Bound by memory: u and the result streamed once, the source gathered near the voxel; the
+// gathers wait for u, so a thread does kApplyPer voxels (a block apart) to have enough loads
+// in flight.  WIDE: 2^31 voxels or more, where an index needs 64 bits.  One voxel per thread
+// with a branch around every corner took 63 us at 264 x 160 x 228 (49 now).
+constexpr int kApplyPer = 2;
+
+template <typename TS, bool WIDE, bool PAIR>
 __global__ __launch_bounds__(kBlock) void k_apply(const float* __restrict__ u, Geom g,
                                                   const TS* __restrict__ src, int interp,
                                                   TS* __restrict__ dst) {
   const long long n = g.n;
-  for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n;
-       i += (long long)gridDim.x * kBlock) {
-    const int x = (int)(i % g.nx);
-    const long long t = i / g.nx;
-    const int y = (int)(t % g.ny);
-    const int z = (int)(t / g.ny);
-    const float dx = u[i] * g.inv_h, dy = u[i + n] * g.inv_h, dz = u[i + 2 * n] * g.inv_h;
-    if (interp == 0) {
-      int cx, cy, cz;
-      float fx, fy, fz;
-      cell_free(x, dx, g.nx, cx, fx);
-      cell_free(y, dy, g.ny, cy, fy);
-      cell_free(z, dz, g.nz, cz, fz);
-      dst[i] = (TS)tri_zero((const float*)src, g, cx, cy, cz, fx, fy, fz);
-    } else {
+  for (long long i0 = (long long)blockIdx.x * kBlock * kApplyPer + threadIdx.x; i0 < n;
+       i0 += (long long)gridDim.x * kBlock * kApplyPer) {
+    float d[kApplyPer][3];
+#pragma unroll
+    for (int k = 0; k < kApplyPer; ++k) {
+      const long long i = i0 + k * kBlock < n ? i0 + k * kBlock : i0;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) d[k][c] = u[i + c * n];
+    }
+    TS res[kApplyPer];
+#pragma unroll
+    for (int k = 0; k < kApplyPer; ++k) {
+      const long long i = i0 + k * kBlock < n ? i0 + k * kBlock : i0;
+      int x, y, z;
+      if (WIDE) {
+        x = (int)(i % g.nx);
+        const long long t = i / g.nx;
+        y = (int)(t % g.ny);
+        z = (int)(t / g.ny);
+      } else {
+        const uint32_t t = fdiv((uint32_t)i, g.fx);
+        x = (int)((uint32_t)i - t * (uint32_t)g.nx);
+        z = (int)fdiv(t, g.fy);
+        y = (int)(t - (uint32_t)z * (uint32_t)g.ny);
+      }
+      const float dx = d[k][0] * g.inv_h, dy = d[k][1] * g.inv_h, dz = d[k][2] * g.inv_h;
       // nearest: index floor(y + 1/2) with y = i + d; rounding uses d alone
       int cx, cy, cz;
       float fx, fy, fz;
-      cell_free(x, dx + 0.5f, g.nx, cx, fx);
-      cell_free(y, dy + 0.5f, g.ny, cy, fy);
-      cell_free(z, dz + 0.5f, g.nz, cz, fz);
-      const bool ok = (unsigned)cx < (unsigned)g.nx && (unsigned)cy < (unsigned)g.ny &&
-                      (unsigned)cz < (unsigned)g.nz;
-      dst[i] = ok ? src[vidx(g, cx, cy, cz)] : (TS)0;
+      cell_free(x, interp == 0 ? dx : dx + 0.5f, g.nx, cx, fx);
+      cell_free(y, interp == 0 ? dy : dy + 0.5f, g.ny, cy, fy);
+      cell_free(z, interp == 0 ? dz : dz + 0.5f, g.nz, cz, fz);
+      if (interp == 0) {
+        res[k] = (TS)tri_zero<PAIR>((const float*)src, g, cx, cy, cz, fx, fy, fz);
+      } else {
+        const bool ok = (unsigned)cx < (unsigned)g.nx && (unsigned)cy < (unsigned)g.ny &&
+                        (unsigned)cz < (unsigned)g.nz;
+        const TS v = src[ok ? vidx(g, cx, cy, cz) : 0u];
+        res[k] = ok ? v : (TS)0;
+      }
     }
+#pragma unroll
+    for (int k = 0; k < kApplyPer; ++k)
+      if (i0 + k * kBlock < n) dst[i0 + k * kBlock] = res[k];
   }
 }
 
@@ -1391,12 +1416,19 @@ void launch_apply(const float* u, int Nx, int Ny, int Nz, float inv_h, const voi
   g.n = (long long)Nx * Ny * Nz;
   g.inv_h = inv_h;
   g.h = 1.f / inv_h;
+  g.fx = make_fastdiv((uint32_t)Nx);
+  g.fy = make_fastdiv((uint32_t)Ny);
+  const bool wide = g.n >= (1LL << 31);
+  const unsigned blocks = grid1d((g.n + kApplyPer - 1) / kApplyPer);
+  auto run = [&](auto kernel, auto* from, auto* to) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, s,
+                       u, g, from, interp, to);
+  };
   if (dtype == 1)
-    hipLaunchKernelGGL(k_apply<int>, dim3(grid1d(g.n)), dim3(kBlock), 0, s, u, g,
-                       (const int*)src, interp, (int*)dst);
+    run(wide ? k_apply<int, true, false> : k_apply<int, false, false>, (const int*)src, (int*)dst);
   else
-    hipLaunchKernelGGL(k_apply<float>, dim3(grid1d(g.n)), dim3(kBlock), 0, s, u, g,
-                       (const float*)src, interp, (float*)dst);
+    run(wide || Nx < 2 ? k_apply<float, true, false> : k_apply<float, false, true>,
+        (const float*)src, (float*)dst);
 }
 
 __global__ __launch_bounds__(kBlock) void k_make_mask(const float* __restrict__ img, long long n,
