@@ -303,6 +303,8 @@ struct Dft<14> : DftPfa<2, 7> {};
 template <>
 struct Dft<15> : DftPfa<3, 5> {};
 template <>
+struct Dft<18> : DftPfa<2, 9> {};
+template <>
 struct Dft<20> : DftPfa<4, 5> {};
 template <>
 struct Dft<28> : DftPfa<4, 7> {};

@@ -61,26 +61,25 @@ bool make_plan(int n, FFTPlan* p) {
   return m == 1;
 }
 
-__global__ void k_twiddles(float2* tw, int n) {
-  for (int m = blockIdx.x * blockDim.x + threadIdx.x; m < n; m += gridDim.x * blockDim.x) {
+// The tables of one level, axis blockIdx.y / 2: twiddles exp(-2 pi i m / n), and the symbol of
+// the periodic 7-point Laplacian along one axis, lambda_d(k) = (2 - 2 cos(2 pi k / n)) / h^2.
+// One launch: six, of a few us each, cost as much as a pass over a small grid.
+__global__ void k_tables(FftTables a) {
+  const int d = blockIdx.y >> 1, n = a.n[d];
+  const int m = blockIdx.x * blockDim.x + threadIdx.x;
+  if (m >= n) return;
+  if (blockIdx.y & 1) {
+    a.lam[d][m] = (2.0 - 2.0 * cospi(2.0 * (double)m / (double)n)) / (a.h * a.h);
+  } else {
     double s, c;
     sincospi(2.0 * (double)m / (double)n, &s, &c);
-    tw[m] = make_float2((float)c, (float)-s);     // exp(-2 pi i m / n)
+    a.tw[d][m] = make_float2((float)c, (float)-s);
   }
 }
 
-void launch_twiddles(float2* tw, int n, hipStream_t s) {
-  hipLaunchKernelGGL(k_twiddles, dim3((n + 255) / 256), dim3(256), 0, s, tw, n);
-}
-
-// lambda_d(k) = (2 - 2 cos(2 pi k / n)) / h^2 : periodic 7-point Laplacian symbol along one axis.
-__global__ void k_lambda(double* lam, int n, double h) {
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x)
-    lam[k] = (2.0 - 2.0 * cospi(2.0 * (double)k / (double)n)) / (h * h);
-}
-
-void launch_lambda(double* lam, int n, double h, hipStream_t s) {
-  hipLaunchKernelGGL(k_lambda, dim3((n + 255) / 256), dim3(256), 0, s, lam, n, h);
+void launch_tables(const FftTables& a, hipStream_t s) {
+  const int nmax = std::max(a.n[0], std::max(a.n[1], a.n[2]));
+  hipLaunchKernelGGL(k_tables, dim3((nmax + 255) / 256, 6), dim3(256), 0, s, a);
 }
 
 // -------------------------------------------------------- radix butterflies --
@@ -363,7 +362,19 @@ constexpr int kCT = 16;   // kx columns per tile of a compile-time pass
   X(100, 10, 10) X(105, 15, 7) X(108, 12, 9) X(112, 16, 7) X(126, 14, 9) X(135, 15, 9) \
   X(144, 12, 12) X(150, 15, 10)
 
-static bool ct_plan(int n, int* n1, int* n2) {
+// Plans of FftPair::alone only.  A plan of its own rounds otherwise than the runtime-planned
+// pass, by FP32 roundings, and a registration's trace holds single values in 64 bits (its least
+// determinant) that would follow; and a factor above 16 needs more threads than the batched
+// launches' 256, whose results are those of single calls bit for bit.  K on 252 x 180 x 200 took
+// 371 us with runtime plans (and a copy of b, and six launches for the tables), 219 with these.
+#define LDDMM_CT_WIDE(X) \
+  X(24, 6, 4) X(25, 5, 5) X(27, 9, 3) X(28, 7, 4) X(30, 6, 5) X(35, 7, 5) X(36, 6, 6) \
+  X(42, 7, 6) X(45, 9, 5) X(48, 8, 6) X(49, 7, 7) X(50, 10, 5) X(54, 9, 6) X(56, 8, 7) \
+  X(63, 9, 7) X(168, 14, 12) X(180, 15, 12) X(192, 16, 12) X(196, 14, 14) X(210, 15, 14) \
+  X(224, 16, 14) X(225, 15, 15) X(256, 16, 16) X(162, 18, 9) X(200, 20, 10) X(216, 18, 12) \
+  X(252, 18, 14) X(270, 18, 15) X(288, 18, 16) X(300, 20, 15) X(320, 20, 16)
+
+static bool ct_plan(const FftPair& f, int n, int* n1, int* n2) {
 #define LDDMM_CT_CASE(N, A, B) \
   if (n == N) {                \
     *n1 = A;                   \
@@ -371,6 +382,9 @@ static bool ct_plan(int n, int* n1, int* n2) {
     return true;               \
   }
   LDDMM_CT_PLANS(LDDMM_CT_CASE)
+  if (f.alone) {
+    LDDMM_CT_WIDE(LDDMM_CT_CASE)
+  }
 #undef LDDMM_CT_CASE
   return false;
 }
@@ -554,16 +568,13 @@ __device__ __forceinline__ bool ct_zK_dispatch(const FftPair& f, int bx, int ky,
 // Row pairs per block of a compile-time x pass: as many as fit 256 threads.
 __host__ __device__ constexpr int kXP(int G) { return kBlock / (3 * G); }
 
-static bool ctx_plan(int n, int* n1, int* n2) {
-#define LDDMM_CT_CASE(N, A, B) \
-  if (n == N) {                \
-    *n1 = A;                   \
-    *n2 = B;                   \
-    return true;               \
+static bool ctx_plan(const FftPair& f, int n, int* n1, int* n2) {
+  if (n == 280) {
+    *n1 = 20;
+    *n2 = 14;
+    return true;
   }
-  LDDMM_CTX_PLANS(LDDMM_CT_CASE)
-#undef LDDMM_CT_CASE
-  return false;
+  return ct_plan(f, n, n1, n2);
 }
 
 // In-LDS transform of the block's lines: natural order in sx[l LS + x] and out.
@@ -1626,10 +1637,10 @@ void set_fft_fused_lds(int bytes) { g_fused_lds = bytes < 0 ? 0 : bytes; }
 // Fill the per-problem tile geometry of the five passes (three when fused).
 void fft_tiles(FftPair& f, FftLaunch* L) {
   int ex, ey, ez, n1, n2;
-  const bool cx = ctx_plan(f.g.nx, &n1, &n2);
+  const bool cx = ctx_plan(f, f.g.nx, &n1, &n2);
   f.ppb = cx ? kXP(n1 > n2 ? n1 : n2) : pairs_per_block(f.g.nx, &ex);
   if (cx) ex = 8;
-  const bool cy = ct_plan(f.g.ny, &n1, &n2), cz = ct_plan(f.g.nz, &n1, &n2);
+  const bool cy = ct_plan(f, f.g.ny, &n1, &n2), cz = ct_plan(f, f.g.nz, &n1, &n2);
   const int ty = cy ? kCT : tile_cols(f.g.ny, 0, &ey);
   const int tz = cz ? kCT : tile_cols(f.g.nz, 1, &ez);
   if (cy) ey = 8;
@@ -1680,10 +1691,17 @@ void launch_fft_x_fwd(const FftPair& f, const FftLaunch& L, hipStream_t s) {
                        dim3(3 * kXP(A > B ? A : B) * (A > B ? A : B)), L.x_lds, s, f);      \
     return;
     LDDMM_CTX_PLANS(LDDMM_CT_CASE)
-#undef LDDMM_CT_CASE
     default:
       break;
   }
+  if (f.alone) {
+    switch (f.g.nx) {
+      LDDMM_CT_WIDE(LDDMM_CT_CASE)
+      default:
+        break;
+    }
+  }
+#undef LDDMM_CT_CASE
   EMAX_SWITCH(L.ex,
     hipLaunchKernelGGL(k_fft_x_fwd<8>, dim3(L.x_tiles), dim3(kBlock), L.x_lds, s, f),
     hipLaunchKernelGGL(k_fft_x_fwd<16>, dim3(L.x_tiles), dim3(kBlock), L.x_lds, s, f),
@@ -1702,10 +1720,17 @@ void launch_fft_y(const FftPair& f, const FftLaunch& L, int inverse, hipStream_t
       hipLaunchKernelGGL((k_fftc_y<A, B, false>), grid, dim3(kCT * (A > B ? A : B)), L.y_lds, s, f); \
     return;
     LDDMM_CT_PLANS(LDDMM_CT_CASE)
-#undef LDDMM_CT_CASE
     default:
       break;
   }
+  if (f.alone) {
+    switch (f.g.ny) {
+      LDDMM_CT_WIDE(LDDMM_CT_CASE)
+      default:
+        break;
+    }
+  }
+#undef LDDMM_CT_CASE
   if (inverse)
     EMAX_SWITCH(L.ey,
       hipLaunchKernelGGL((k_fft_y<8, true>), grid, dim3(kBlock), L.y_lds, s, f),
@@ -1726,10 +1751,17 @@ void launch_fft_z_K(const FftPair& f, const FftLaunch& L, hipStream_t s) {
     hipLaunchKernelGGL((k_fftc_zK<A, B>), grid, dim3(kCT * (A > B ? A : B)), L.z_lds, s, f); \
     return;
     LDDMM_CT_PLANS(LDDMM_CT_CASE)
-#undef LDDMM_CT_CASE
     default:
       break;
   }
+  if (f.alone) {
+    switch (f.g.nz) {
+      LDDMM_CT_WIDE(LDDMM_CT_CASE)
+      default:
+        break;
+    }
+  }
+#undef LDDMM_CT_CASE
   EMAX_SWITCH(L.ez,
     hipLaunchKernelGGL(k_fft_z_K<8>, grid, dim3(kBlock), L.z_lds, s, f),
     hipLaunchKernelGGL(k_fft_z_K<16>, grid, dim3(kBlock), L.z_lds, s, f),
@@ -1754,10 +1786,17 @@ void launch_fft_x_inv(const FftPair& f, const FftLaunch& L, const UpdArgs& u, hi
                        dim3(3 * kXP(A > B ? A : B) * (A > B ? A : B)), L.x_lds, s, f, u);   \
     return;
     LDDMM_CTX_PLANS(LDDMM_CT_CASE)
-#undef LDDMM_CT_CASE
     default:
       break;
   }
+  if (f.alone) {
+    switch (f.g.nx) {
+      LDDMM_CT_WIDE(LDDMM_CT_CASE)
+      default:
+        break;
+    }
+  }
+#undef LDDMM_CT_CASE
   EMAX_SWITCH(L.ex,
     hipLaunchKernelGGL(k_fft_x_inv<8>, dim3(L.x_tiles), dim3(kBlock), L.x_lds, s, f, u),
     hipLaunchKernelGGL(k_fft_x_inv<16>, dim3(L.x_tiles), dim3(kBlock), L.x_lds, s, f, u),

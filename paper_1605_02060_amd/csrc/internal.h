@@ -169,6 +169,7 @@ struct FftPair {
   int lgTXy, nbx_y;        // y pass: log2 tile width, tiles along kx
   int lgTXz, nbx_z;        // z pass
   int fused;               // x and y in one pass each way (a plane of one component in LDS)
+  int alone;               // never in a batched launch, and only FP32 fields come of it: every plan may be used
   const State* st;
   int need_mode;
 };
@@ -262,8 +263,13 @@ void launch_copy_iterate(const float* vA, const float* vB, const State* st, floa
 
 // fft.hip
 bool make_plan(int n, FFTPlan* p);
-void launch_twiddles(float2* tw, int n, hipStream_t s);
-void launch_lambda(double* lam, int n, double h, hipStream_t s);
+struct FftTables {
+  float2* tw[3];
+  double* lam[3];
+  int n[3];
+  double h;
+};
+void launch_tables(const FftTables& a, hipStream_t s);
 void fft_tiles(FftPair& f, FftLaunch* L);
 void set_fft_fused_lds(int bytes);
 void launch_fft_x_fwd(const FftPair& f, const FftLaunch& L, hipStream_t s);

@@ -306,6 +306,7 @@ struct Ctx {
   float2* S;
   double alpha, gamma, sigma;
   int guard;
+  int alone;                       // FftPair::alone
   // time-batched K (levels in cfg.kt_mask): body forces [T][3][n], spectra
   // [T][3][nspec], one device table per time step, and the host copies behind
   // them (one set per table build, kept until the call returns, so that no
@@ -351,11 +352,15 @@ static void bind(Ctx& c, void* ws) {
 }
 
 static void level_tables(Ctx& c, const Level& L, hipStream_t s) {
+  FftTables a{};
   const int P[3] = {L.g.nx, L.g.ny, L.g.nz};
   for (int d = 0; d < 3; ++d) {
-    launch_twiddles(c.tw[d], P[d], s);
-    launch_lambda(c.lam[d], P[d], (double)L.g.h, s);
+    a.tw[d] = c.tw[d];
+    a.lam[d] = c.lam[d];
+    a.n[d] = P[d];
   }
+  a.h = (double)L.g.h;
+  launch_tables(a, s);
 }
 
 // Forward sweep of the velocity selected by st->eval (vA/vB) for steps
@@ -433,6 +438,7 @@ static FftPair make_fft(Ctx& c, int li, int need_mode, FftLaunch* L) {
   f.S = c.S;
   f.st = c.st;
   f.need_mode = need_mode;
+  f.alone = c.alone;
   fft_tiles(f, L);
   return f;
 }
@@ -1218,6 +1224,7 @@ static int gradient_call(const lddmm_problem* p, const lddmm_params* prm, int32_
     launch_energy_out_checked(c.st, c.misc + 1, out4, s);
     return hip_status();
   }
+  c.alone = 1;                              // K reaches the FP32 gradient only
   level_tables(c, c.cfg.lv[0], s);
   forward_sweep(c, 0, p->v, p->v, false, s);
   decide(c, 0, 1, c.trace, s);
@@ -1288,9 +1295,15 @@ int lddmm_smooth(const int32_t P[3], double spacing, double alpha, double gamma,
   c.S = (float2*)(w + off);
   c.alpha = alpha;
   c.gamma = gamma;
+  c.alone = 1;
   launch_level_begin(c.st, 1.0, 0, 0, s);
   level_tables(c, L, s);
-  launch_copy(b, c.b, 3 * L.g.n, s);
+  // the first pass reads b where it is; its 16-byte loads want it (and so every row and
+  // component, when 4 divides P[0]) on a 16-byte boundary
+  if (((uintptr_t)b & 15) == 0)
+    c.b = const_cast<float*>(b);
+  else
+    launch_copy(b, c.b, 3 * L.g.n, s);
   UpdArgs u{};
   u.kind = UPD_WRITE_KB;
   u.out = out;
