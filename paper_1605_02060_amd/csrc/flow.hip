@@ -704,6 +704,31 @@ __device__ __forceinline__ SlabTile slab_tile(const Geom& g, int block) {
 }
 
 
+// A plane of a ring is loaded with the thread's offsets in vector registers, computed once, and
+// the plane's in a scalar one: an element outside the grid has an offset past every buffer, which
+// reads as 0, so a load costs a select and no branch.
+constexpr uint32_t kOutsideBytes = 4u * kOutside;
+
+__device__ __forceinline__ uint32_t plane_bytes(const Geom& g, int p) {
+  return __builtin_amdgcn_readfirstlane(4u * (uint32_t)p * (uint32_t)(g.nx * g.ny));
+}
+
+__device__ __forceinline__ float bld_at(rsrc_t r, uint32_t bytes, uint32_t plane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, bytes, plane, 0));
+}
+
+// Where the two planes of a cell lie in a ring of three planes of `plane` values: cell plane z
+// (at_z) or z - 1 of step z.  The slots are the same for the whole block, so a cell costs a
+// select a plane (a remainder by 3 of its own plane each cost more than its reads).
+struct RingCell {
+  int a, b;
+  __device__ __forceinline__ RingCell(bool at_z, int z, int plane, int in_plane) {
+    const int s0 = z % 3 * plane, sm = (z + 2) % 3 * plane, sp = (z + 1) % 3 * plane;
+    a = in_plane + (at_z ? s0 : sm);
+    b = in_plane + (at_z ? sp : s0);
+  }
+};
+
 // Ring of map planes (3 components, halo kBH, clamped) staged through registers.
 // Slot-major layout: element e of a staged plane (component, window row, window
 // column: the order in which the block's threads load them) sits at s[slot] + e.
@@ -712,40 +737,43 @@ __device__ __forceinline__ SlabTile slab_tile(const Geom& g, int block) {
 struct MapRing {
   float (*s)[3][kBYH][kBXH];     // [slot][component][row][column]
   float reg[kURegs];
-  uint32_t off[kURegs];          // in-plane element offset of element r, component included,
+  uint32_t off[kURegs];          // in-plane byte offset of element r, component included,
                                  // of the periodic image of its (x, y)
-  uint32_t ok;                   // bit r: element r lies in the grid's (x, y) range
+  bool ok[kURegs];               // element r lies in the grid's (x, y) range
   __device__ __forceinline__ void init(const Geom& g, uint32_t n, int x0, int y0) {
-    ok = 0u;
 #pragma unroll
     for (int r = 0; r < kURegs; ++r) {
       const int e = threadIdx.x + r * kBlock;
-      off[r] = 0u;
+      off[r] = kOutsideBytes;
+      ok[r] = false;
       if (e < kUPlane) {
         const int c = e / (kBYH * kBXH), rem = e - c * (kBYH * kBXH);
         const int ly = rem / kBXH, lx = rem - ly * kBXH;
         const int gx = x0 - kBH + lx, gy = y0 - kBH + ly;
         const int px = (gx % g.nx + g.nx) % g.nx, py = (gy % g.ny + g.ny) % g.ny;
-        off[r] = (uint32_t)c * n + (uint32_t)(py * g.nx + px);
-        if ((unsigned)gx < (unsigned)g.nx && (unsigned)gy < (unsigned)g.ny) ok |= 1u << r;
+        off[r] = 4u * ((uint32_t)c * n + (uint32_t)(py * g.nx + px));
+        ok[r] = (unsigned)gx < (unsigned)g.nx && (unsigned)gy < (unsigned)g.ny;
       }
     }
   }
   // Plane p into registers (0 outside the grid).
   __device__ __forceinline__ void fetch(rsrc_t U, const Geom& g, int p) {
-    const bool pin = p >= 0 && p < g.nz;
-    const uint32_t po = pin ? (uint32_t)p * (uint32_t)(g.nx * g.ny) : 0u;
+    if (p >= 0 && p < g.nz) {
+      const uint32_t po = plane_bytes(g, p);
 #pragma unroll
-    for (int r = 0; r < kURegs; ++r) reg[r] = (pin && ((ok >> r) & 1u)) ? bld(U, off[r] + po) : 0.f;
+      for (int r = 0; r < kURegs; ++r) reg[r] = bld_at(U, ok[r] ? off[r] : kOutsideBytes, po);
+    } else {
+#pragma unroll
+      for (int r = 0; r < kURegs; ++r) reg[r] = 0.f;
+    }
   }
   // Plane p (-nz <= p < 2 nz) of a periodic field into registers, the window
   // wrapped around the grid in x, y and z.
   __device__ __forceinline__ void fetch_periodic(rsrc_t U, const Geom& g, int p) {
     const int pw = p < 0 ? p + g.nz : (p >= g.nz ? p - g.nz : p);
-    const uint32_t po = (uint32_t)pw * (uint32_t)(g.nx * g.ny);
+    const uint32_t po = plane_bytes(g, pw);
 #pragma unroll
-    for (int r = 0; r < kURegs; ++r)
-      reg[r] = (threadIdx.x + r * kBlock < kUPlane) ? bld(U, off[r] + po) : 0.f;
+    for (int r = 0; r < kURegs; ++r) reg[r] = bld_at(U, off[r], po);
   }
   // Plane p >= 0 into slot p mod 2 of a two-slot ring of the same window.
   __device__ __forceinline__ void put2(int p) {
@@ -770,15 +798,14 @@ struct MapRing {
   __device__ __forceinline__ bool sample3(int x0, int y0, int z, int cx, int cy, int cz, float fx,
                                           float fy, float fz, float out[3]) const {
     const int wx = cx - (x0 - kBH), wy = cy - (y0 - kBH);
-    if (!(wx >= 0 && wx + 1 < kBXH && wy >= 0 && wy + 1 < kBYH && cz >= z - kBH &&
-          cz + 1 <= z + kBH))
+    if ((unsigned)wx >= kBXH - 1 || (unsigned)wy >= kBYH - 1 || (unsigned)(cz - (z - kBH)) >= 2 * kBH)
       return false;
-    const int za = cz % kBRing, zb = (cz + 1) % kBRing;
+    const RingCell w(cz == z, z, 3 * kBYH * kBXH, wy * kBXH + wx);
+    const float *pa = &s[0][0][0][0] + w.a, *pb = &s[0][0][0][0] + w.b;
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-      out[c] = lerp8(s[za][c][wy][wx], s[za][c][wy][wx + 1], s[za][c][wy + 1][wx],
-                     s[za][c][wy + 1][wx + 1], s[zb][c][wy][wx], s[zb][c][wy][wx + 1],
-                     s[zb][c][wy + 1][wx], s[zb][c][wy + 1][wx + 1], fx, fy, fz);
+    for (int c = 0; c < 3; ++c, pa += kBYH * kBXH, pb += kBYH * kBXH)
+      out[c] = lerp8(pa[0], pa[1], pa[kBXH], pa[kBXH + 1], pb[0], pb[1], pb[kBXH], pb[kBXH + 1], fx,
+                     fy, fz);
     return true;
   }
 };
@@ -791,23 +818,23 @@ struct HaloRing {
   static constexpr int kRegs = (kPlane + kBlock - 1) / kBlock;
   float (*s)[K][kBYJ][kBXJ];     // [slot][component][row][column]
   float reg[kRegs];
-  uint32_t off[kRegs];           // in-plane element offset of element r
-  uint32_t ok, c1;               // bit r: in the grid's (x, y) range / of component 1
+  uint32_t off[kRegs];           // in-plane byte offset of element r
+  bool ok[kRegs];                // element r lies in the grid's (x, y) range
+  bool c1[kRegs];                // element r is of component 1
   __device__ __forceinline__ void init(const Geom& g, int x0, int y0) {
-    ok = 0u;
-    c1 = 0u;
 #pragma unroll
     for (int r = 0; r < kRegs; ++r) {
       const int e = threadIdx.x + r * kBlock;
-      off[r] = 0u;
+      off[r] = kOutsideBytes;
+      ok[r] = c1[r] = false;
       if (e < kPlane) {
         const int c = e / (kBYJ * kBXJ), rem = e - c * (kBYJ * kBXJ);
         const int ly = rem / kBXJ, lx = rem - ly * kBXJ;
         const int gx = x0 - 1 + lx, gy = y0 - 1 + ly;
         if ((unsigned)gx < (unsigned)g.nx && (unsigned)gy < (unsigned)g.ny) {
-          off[r] = (uint32_t)(gy * g.nx + gx);
-          ok |= 1u << r;
-          if (c > 0) c1 |= 1u << r;
+          off[r] = 4u * (uint32_t)(gy * g.nx + gx);
+          ok[r] = true;
+          c1[r] = c > 0;
         }
       }
     }
@@ -817,23 +844,30 @@ struct HaloRing {
   __device__ __forceinline__ void init_from(const MapRing& m) {
     static_assert(K == 1 && kBH == 1 && kBXJ == kBXH && kBYJ == kBYH && kRegs <= kURegs,
                   "the same window");
-    ok = 0u;
-    c1 = 0u;
 #pragma unroll
     for (int r = 0; r < kRegs; ++r) {
       off[r] = m.off[r];
-      if (threadIdx.x + r * kBlock < kPlane) ok |= m.ok & (1u << r);
+      ok[r] = threadIdx.x + r * kBlock < kPlane && m.ok[r];
+      c1[r] = false;
     }
   }
   // Plane p of every component into registers; component c is read through R[c].
   __device__ __forceinline__ void fetch(const rsrc_t* R, const Geom& g, int p) {
-    const bool pin = p >= 0 && p < g.nz;
-    const uint32_t po = pin ? (uint32_t)p * (uint32_t)(g.nx * g.ny) : 0u;
+    if (p >= 0 && p < g.nz) {
+      const uint32_t po = plane_bytes(g, p);
 #pragma unroll
-    for (int r = 0; r < kRegs; ++r) {
-      float val = 0.f;
-      if (pin && ((ok >> r) & 1u)) val = bld(R[K > 1 && ((c1 >> r) & 1u) ? 1 : 0], off[r] + po);
-      reg[r] = val;
+      for (int r = 0; r < kRegs; ++r) {
+        if (K == 1) {
+          reg[r] = bld_at(R[0], ok[r] ? off[r] : kOutsideBytes, po);
+        } else {
+          const float v0 = bld_at(R[0], ok[r] && !c1[r] ? off[r] : kOutsideBytes, po);
+          const float v1 = bld_at(R[K - 1], c1[r] ? off[r] : kOutsideBytes, po);
+          reg[r] = c1[r] ? v1 : v0;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < kRegs; ++r) reg[r] = 0.f;
     }
   }
   // Plane p >= -1 into slot (p + 3) mod 3 (the planes outside the grid as zeros).
@@ -849,17 +883,17 @@ struct HaloRing {
   // columns x0 - 1 .. x0 + kBX, rows y0 - 1 .. y0 + kBY, planes z - 1 .. z + 1.
   __device__ __forceinline__ static bool covers(int x0, int y0, int z, int cx, int cy, int cz) {
     const int wx = cx - (x0 - 1), wy = cy - (y0 - 1);
-    return wx >= 0 && wx + 1 < kBXJ && wy >= 0 && wy + 1 < kBYJ && cz >= z - 1 && cz <= z;
+    return (unsigned)wx < kBXJ - 1 && (unsigned)wy < kBYJ - 1 && (unsigned)(cz - (z - 1)) < 2;
   }
   // Trilinear sample of component c at a covered cell, zero outside the grid (the
   // staged planes hold zeros there), corners in the order of sample().
-  __device__ __forceinline__ float lerp(int c, int x0, int y0, int cx, int cy, int cz, float fx,
-                                        float fy, float fz) const {
+  __device__ __forceinline__ float lerp(int c, int x0, int y0, int z, int cx, int cy, int cz,
+                                        float fx, float fy, float fz) const {
     const int wx = cx - (x0 - 1), wy = cy - (y0 - 1);
-    const int za = (cz + 3) % 3, zb = (cz + 4) % 3;
-    return lerp8(s[za][c][wy][wx], s[za][c][wy][wx + 1], s[za][c][wy + 1][wx],
-                 s[za][c][wy + 1][wx + 1], s[zb][c][wy][wx], s[zb][c][wy][wx + 1],
-                 s[zb][c][wy + 1][wx], s[zb][c][wy + 1][wx + 1], fx, fy, fz);
+    const RingCell w(cz == z, z, kPlane, (c * kBYJ + wy) * kBXJ + wx);
+    const float *pa = &s[0][0][0][0] + w.a, *pb = &s[0][0][0][0] + w.b;
+    return lerp8(pa[0], pa[1], pa[kBXJ], pa[kBXJ + 1], pb[0], pb[1], pb[kBXJ], pb[kBXJ + 1], fx, fy,
+                 fz);
   }
 };
 
@@ -1116,7 +1150,7 @@ struct StagedTemplateSampler {
     cell_free(z, dz, g.nz, cz, fz);
     if (HaloRing<NC>::covers(x0, y0, z, cx, cy, cz)) {
 #pragma unroll
-      for (int c = 0; c < NC; ++c) out[c] = rt.lerp(c, x0, y0, cx, cy, cz, fx, fy, fz);
+      for (int c = 0; c < NC; ++c) out[c] = rt.lerp(c, x0, y0, z, cx, cy, cz, fx, fy, fz);
     } else {
       GlobalTemplateSampler<NC>{f, g}(x, y, z, dx, dy, dz, out);
     }
