@@ -697,6 +697,149 @@ __global__ __launch_bounds__(kBlk) void k_conv_halo(HaloArgs a) {
   if constexpr (OP != H_DG2) store(1, 0, 0, 0);
 }
 
+// ---------------------------------------------------- two source channels, stride 1 ----
+// The network's first layer.  A voxel's two channels are one 32-bit word, so a block stages the
+// words of a P2X x P2Y x P2Z tile and its halo in LDS and a fragment is four reads at offsets
+// that belong to the lane alone (the taps of its k-values), the tile's place an immediate; the 54
+// weights of a row stay in two registers' worth of fragments.  Bound by the writes (32 B per
+// voxel for 16 rows).  Read straight from memory (the fragment kernel: eight gathers of 4 B per
+// lane for 16 voxels, each as dear to L1 as one of 16 B) 8 x 96^3 took 180 us and one 29:
+// 70 and 15.5 now (93 and 19 with four planes to a block and stores of 8 B).
+// k order and instruction as there, so the same bits.
+constexpr int P2X = 32, P2Y = 4, P2Z = 8, P2W = P2X + 4;   // P2W: words of a staged row
+
+__global__ __launch_bounds__(kBlk) void k_conv_two(HaloArgs a) {
+  constexpr int SY = P2Y + 2, SZ = P2Z + 2, PLANE = SY * P2W;
+  __shared__ uint32_t tile[SZ * PLANE];
+  const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m0 = blockIdx.y * 16;
+  int b = xcd_block(blockIdx.x, gridDim.x);
+  if (b >= a.ntiles) return;
+  const int x0 = (b % a.ntx) * P2X;
+  b /= a.ntx;
+  const int y0 = (b % a.nty) * P2Y;
+  b /= a.nty;
+  const int z0 = (b % a.ntz) * P2Z;
+  b /= a.ntz;                                                // the sample
+  const rsrc_t Sr = __builtin_amdgcn_make_buffer_rsrc((void*)a.src, (short)0, (int)a.src_bytes,
+                                                      0x00020000);
+  constexpr int PER = (SZ * PLANE + kBlk - 1) / kBlk;
+  uint32_t st[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int e = threadIdx.x + i * kBlk;
+    const int q = e / P2W, x = e - q * P2W, z = q / SY, y = q - z * SY;
+    const int iz = z0 - 1 + z, iy = y0 - 1 + y, ix = x0 - 1 + x;
+    const bool in = e < SZ * PLANE && (unsigned)iz < (unsigned)a.sd &&
+                    (unsigned)iy < (unsigned)a.sh && (unsigned)ix < (unsigned)a.sw;
+    st[i] = bld4(Sr, in ? (uint32_t)(((b * a.sd + iz) * a.sh + iy) * a.sw + ix) * 4u : kOut);
+  }
+  // weights: k = 32 step + 8 g + e of row m0 + r16, zero past the row's 54
+  bf16x8 wf[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (m0 + r16 < a.M) {
+      const u16* p = a.w + (long)(m0 + r16) * 54;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int k = 32 * h + 8 * g + 2 * e;
+        if (k < 54) v[e] = p[k] | (uint32_t)p[k + 1] << 16;
+      }
+    }
+    wf[h] = __builtin_bit_cast(bf16x8, v);
+  }
+  // this lane's words of a fragment: tap j = 16 step + 4 g + i at its voxel; past the taps, zero
+  int off[2][4];
+  bool tap[4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int j = 16 * h + 4 * g + i, c = j < 27 ? j : 0;
+      const int jz = c / 9, jy = (c / 3) % 3, jx = c % 3;
+      off[h][i] = (wave + jz) * PLANE + jy * P2W + jx + r16;   // a wavefront takes one plane
+      if (h == 1) tap[i] = j < 27;
+    }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int e = threadIdx.x + i * kBlk;
+    if (e < SZ * PLANE) tile[e] = st[i];
+  }
+  __syncthreads();
+  // pairs of tiles along x: with 16 rows of bf16, rows of lanes exchanged between the two, so that
+  // a lane stores eight channels of one voxel at once
+  const bool wide = a.vec && !a.out_f32 && a.M % 16 == 0 && ((uintptr_t)a.out & 15) == 0;
+  float bias[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (a.bias && m0 + 4 * g + r < a.M) bias[r] = a.bias[m0 + 4 * g + r];
+  for (int z = wave; z < P2Z; z += 4) {
+    const int oz = z0 + z;
+    if (oz >= a.fd) break;
+#pragma unroll
+    for (int y = 0; y < P2Y; ++y) {
+      const int oy = y0 + y;
+      f32x4 acc[P2X / 16];
+#pragma unroll
+      for (int xh = 0; xh < P2X / 16; ++xh) {
+        const uint32_t* p = tile + (z - wave) * PLANE + y * P2W + 16 * xh;
+        u32x4 f[2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          f[0][i] = p[off[0][i]];
+          const uint32_t v = p[off[1][i]];
+          f[1][i] = tap[i] ? v : 0u;
+        }
+        acc[xh] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          acc[xh] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              wf[h], __builtin_bit_cast(bf16x8, f[h]), acc[xh], 0, 0, 0);
+      }
+      const int row = ((b * a.fd + oz) * a.fh + oy) * a.fw;
+      if (wide) {
+        uint32_t w[2][2];
+#pragma unroll
+        for (int xh = 0; xh < 2; ++xh) {
+          float v[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            v[r] = acc[xh][r];
+            if (a.bias) v[r] += bias[r];
+            if (a.relu) v[r] = fmaxf(v[r], 0.f);
+          }
+          w[xh][0] = pack_bf(v[0], v[1]);
+          w[xh][1] = pack_bf(v[2], v[3]);
+        }
+        // lane rows 0 .. 3 hold channels 4 g of both tiles; after the swap rows 0, 2 hold eight
+        // channels of the first tile's voxel and rows 1, 3 of the second's
+        const auto lo = __builtin_amdgcn_permlane16_swap(w[0][0], w[1][0], false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(w[0][1], w[1][1], false, false);
+        const u32x4 q = {lo[0], hi[0], lo[1], hi[1]};
+        const int ox = x0 + 16 * (g & 1) + r16;
+        if (oy < a.fh && ox < a.fw)
+          *reinterpret_cast<u32x4*>((u16*)a.out + (long)(row + ox) * a.M + m0 + 8 * (g >> 1)) = q;
+      } else {
+#pragma unroll
+        for (int xh = 0; xh < 2; ++xh) {
+          const int ox = x0 + 16 * xh + r16;
+          conv_store<false>(a, acc[xh], oy < a.fh && ox < a.fw ? row + ox : -1, m0 + 4 * g);
+        }
+      }
+    }
+  }
+}
+
+void launch_two(HaloArgs h, int samples, hipStream_t s) {
+  h.ntx = (h.vw + P2X - 1) / P2X;
+  h.nty = (h.vh + P2Y - 1) / P2Y;
+  h.ntz = (h.vd + P2Z - 1) / P2Z;
+  h.ntiles = h.ntx * h.nty * h.ntz * samples;
+  hipLaunchKernelGGL(k_conv_two, dim3(round_xcd(h.ntiles), (h.M + 15) / 16), dim3(kBlk), 0, s, h);
+}
+
 template <int OP, int S, int NB, int MT, int WM>
 void launch_halo_k(HaloArgs h, int samples, hipStream_t s) {
   using G = HaloGeom<OP, S, NB, MT * WM>;
@@ -718,14 +861,35 @@ bool try_halo(const HaloArgs& h, int samples, hipStream_t s) {
   }
 }
 
+// Blocks of a variant; 0: it has none.
+template <int OP, int S, int NB, int MT, int WM>
+long long halo_blocks(const HaloArgs& h, int samples) {
+  using G = HaloGeom<OP, S, NB, MT * WM>;
+  if (!G::fits) return 0;
+  return (long long)((h.vw + HX - 1) / HX) * ((h.vh + HY - 1) / HY) * ((h.vd + G::TZ - 1) / G::TZ) *
+         samples * ((h.M + 16 * MT * WM - 1) / (16 * MT * WM));
+}
+
+// Rows of a block: as many as there are up to 192, so that a tile is staged once for all; but
+// while that leaves half of the 256 CUs without a block, half as many (the staging is repeated,
+// the products, which take most of the time, are shared out).  One 96^3 sample through the
+// network: 43 -> 32 us in the decoder, 21 -> 12 and 15 -> 11 in the deepest encoder and the head.
 template <int OP, int S, int NB>
 bool launch_halo_m(const HaloArgs& h, int samples, hipStream_t s) {
+  constexpr int kFew = 128;
   if (h.M <= 16) return try_halo<OP, S, NB, 1, 1>(h, samples, s);
-  if (h.M <= 32) return try_halo<OP, S, NB, 1, 2>(h, samples, s);
+  if (h.M <= 32 || halo_blocks<OP, S, NB, 2, 2>(h, samples) <= kFew) {
+    if (halo_blocks<OP, S, NB, 1, 2>(h, samples) <= kFew)
+      return try_halo<OP, S, NB, 1, 1>(h, samples, s);
+    return try_halo<OP, S, NB, 1, 2>(h, samples, s);
+  }
   if (h.M <= 64) return try_halo<OP, S, NB, 2, 2>(h, samples, s);
   if constexpr (NB <= 2) {         // with more channels the blocks of 64 rows fill the CU's LDS
-    if (h.M % 192 == 0 && try_halo<OP, S, NB, 6, 2>(h, samples, s)) return true;
-    if (try_halo<OP, S, NB, 4, 2>(h, samples, s)) return true;
+    if (h.M % 192 == 0 && halo_blocks<OP, S, NB, 6, 2>(h, samples) > kFew &&
+        try_halo<OP, S, NB, 6, 2>(h, samples, s))
+      return true;
+    if (halo_blocks<OP, S, NB, 4, 2>(h, samples) > kFew && try_halo<OP, S, NB, 4, 2>(h, samples, s))
+      return true;
   }
   return try_halo<OP, S, NB, 2, 2>(h, samples, s);
 }
@@ -774,6 +938,11 @@ bool launch_halo(const FragArgs& f, bool dg, int stride, int samples, hipStream_
   h.add_stride = f.add_stride;
   h.add_off = f.add_off;
   h.vec = f.vec;
+  if (f.C == 2) {
+    if (dg || stride != 1) return false;
+    launch_two(h, samples, s);
+    return true;
+  }
   if (cls) return launch_halo_c<H_DG2, 1>(f.C, h, samples, s);
   if (dg) return launch_halo_c<H_DG1, 1>(f.C, h, samples, s);
   return stride == 2 ? launch_halo_c<H_FWD, 2>(f.C, h, samples, s)
@@ -820,7 +989,7 @@ bool launch_conv_frag(int op, const ConvArgs& a, hipStream_t s) {
   f.vec = f.M % 4 == 0 && ((uintptr_t)a.out & (a.out_f32 ? 15 : 7)) == 0 &&
           ((uintptr_t)a.mask & 7) == 0 &&
           (!a.add || (((uintptr_t)a.add & 7) == 0 && a.add_stride % 4 == 0 && a.add_off % 4 == 0));
-  if (km == KM_32 && launch_halo(f, dg, a.s, a.n, s)) return true;
+  if ((km == KM_32 || f.C == 2) && launch_halo(f, dg, a.s, a.n, s)) return true;
   const int mt = f.M <= 16 ? 1 : (f.M <= 32 ? 2 : (f.M <= 64 ? 4 : (f.M % 96 == 0 ? 6 : 8)));
   if (dg && a.s == 2) {
     Problem p{};
