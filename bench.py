@@ -701,15 +701,12 @@ MASK_TAU, MASK_OPEN, MASK_CLOSE = 0.1, 0.05, 0.125   # threshold; 50 um and 125 
 # Algorithmic HBM bytes per voxel of each call (FP32 inputs and outputs; the
 # bit-packed intermediates are 1/8 byte per voxel and pass):
 #  target mask      : read the image 4, write the mask 4
-#  surface distance : read both masks 8; per direction write and read the row
-#                     distances 8 and write the column distances 4 (the z pass
-#                     reads them only at surface voxels): 8 + 2 * 12
-MASK_ALG_BYTES = {"target_mask": 8.0, "surface_distance": 32.0}
-# The surface-distance y pass is integer ALU work: for every voxel and every row
-# y' of its column, a difference, a multiply-add and a minimum.
-MASK_Y_OPS = 3
-# 32-bit integer VALU peak: 256 CUs x 4 SIMDs x 16 lanes per clock x 2.4 GHz.
-ALU_INT32_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
+#  surface distance : read both masks 8; per direction write the column distances 4
+#                     (the z pass reads them only at surface voxels): 8 + 2 * 4
+MASK_ALG_BYTES = {"target_mask": 8.0, "surface_distance": 16.0}
+# The x + y distance pass writes the column distances of both directions; how many rows of a
+# column it looks at depends on the masks, so its rate is given in bytes.
+MASK_XY_BYTES = 8.0
 
 
 def masks_image(pair):
@@ -796,8 +793,7 @@ def bench_masks(args):
         per[name] = {"avg_us": 1e3 * avg_ms,
                      "GBs": MASK_ALG_BYTES[name] * n / (avg_ms * 1e-3) / 1e9}
     y_ms = ypass["ms"] / max(ypass["launches"], 1)
-    y_ops = MASK_Y_OPS * pair.shape[1] * n                 # 3 integer ops per (voxel, row)
-    y_achieved = y_ops / (y_ms * 1e-3) / 1e12
+    y_achieved = MASK_XY_BYTES * n / (y_ms * 1e-3) / 1e9
     cpu = None
     if not args.no_cpu_baseline:
         log("cpu baseline (oracle) ...")
@@ -821,10 +817,9 @@ def bench_masks(args):
                                f"264x160x228 at 50 um; {MASK_CALLS} of each per step",
                    "grid": [264, 160, 228], "spacing_mm": SPACING, "tau": MASK_TAU,
                    "open_radius_mm": MASK_OPEN, "close_radius_mm": MASK_CLOSE},
-        "roofline": {"bound": "alu", "achieved": y_achieved, "peak": ALU_INT32_PEAK_TOPS,
-                     "unit": "Tops/s", "frac": y_achieved / ALU_INT32_PEAK_TOPS, "traffic": None,
-                     "kernel": "k_edt_y",
-                     "alg_ops_per_voxel": MASK_Y_OPS * pair.shape[1],
+        "roofline": {"bound": "hbm", "achieved": y_achieved, "peak": HBM_PEAK_GBS,
+                     "unit": "GB/s", "frac": y_achieved / HBM_PEAK_GBS, "traffic": None,
+                     "kernel": "k_edt_xy", "alg_bytes_per_voxel": MASK_XY_BYTES,
                      "avg_launch_ms": y_ms, "launches": ypass["launches"],
                      "voxels_per_launch": n},
         "calls": per,
