@@ -362,11 +362,13 @@ constexpr int kCT = 16;   // kx columns per tile of a compile-time pass
   X(100, 10, 10) X(105, 15, 7) X(108, 12, 9) X(112, 16, 7) X(126, 14, 9) X(135, 15, 9) \
   X(144, 12, 12) X(150, 15, 10)
 
-// Plans of FftPair::alone only.  A plan of its own rounds otherwise than the runtime-planned
-// pass, by FP32 roundings, and a registration's trace holds single values in 64 bits (its least
+// Plans of FftPair::alone only; their z passes form K's symbol in FP64, as the runtime-planned
+// ones do.  A plan of its own adds its lines' FP32 values in another order than the
+// runtime-planned pass, and a registration's trace holds single values in 64 bits (its least
 // determinant) that would follow; and a factor above 16 needs more threads than the batched
 // launches' 256, whose results are those of single calls bit for bit.  K on 252 x 180 x 200 took
-// 371 us with runtime plans (and a copy of b, and six launches for the tables), 219 with these.
+// 371 us with runtime plans (and a copy of b, and six launches for the tables), 223 with these
+// (220 with the symbol in FP32).
 #define LDDMM_CT_WIDE(X) \
   X(24, 6, 4) X(25, 5, 5) X(27, 9, 3) X(28, 7, 4) X(30, 6, 5) X(35, 7, 5) X(36, 6, 6) \
   X(42, 7, 6) X(45, 9, 5) X(48, 8, 6) X(49, 7, 7) X(50, 10, 5) X(54, 9, 6) X(56, 8, 7) \
@@ -390,9 +392,10 @@ static bool ct_plan(const FftPair& f, int n, int* n1, int* n2) {
 }
 
 // LDS of one compile-time tile: the exchange, the twiddles and (z pass) the
-// K symbol tables.
+// K symbol tables: n + kCT floats, or n doubles for the lengths of FftPair::alone.
 static size_t ct_lds_bytes(int n) {
-  return sizeof(float2) * ((size_t)kCT * (n + 1) + n) + sizeof(float) * ((size_t)n + kCT);
+  const size_t sym = std::max(sizeof(float) * ((size_t)n + kCT), sizeof(double) * (size_t)n);
+  return sizeof(float2) * ((size_t)kCT * (n + 1) + n) + sym;
 }
 
 // y pass (forward, or inverse through conj(DFT(conj X))) of columns
@@ -439,7 +442,10 @@ __device__ __forceinline__ void ct_y_body(const FftPair& f, int bx, int zslab, i
 
 // z pass: forward transform, K_hat / |P| (and conj), forward transform of the
 // conjugate, conj on the way out: N_z IDFT_z(K_hat X / |P|).
-template <int N1, int N2>
+// SYM64: K_hat / |P| from FP64 terms, rounded once, as in zK_body (the lengths of
+// FftPair::alone, which replace that pass); else two FP32 terms added, and the hardware
+// reciprocal of their square, which is infinite for gamma below about 1e-19.
+template <int N1, int N2, bool SYM64>
 __device__ __forceinline__ void ct_zK_body(const FftPair& f, int bx, int ky, int comp) {
   constexpr int N = N1 * N2, LS = N + 1;
   extern __shared__ float2 sm[];
@@ -447,6 +453,7 @@ __device__ __forceinline__ void ct_zK_body(const FftPair& f, int bx, int ky, int
   float2* stw = sm + kCT * LS;
   float* saz = reinterpret_cast<float*>(stw + N);
   float* scxy = saz + N;
+  double* slz = reinterpret_cast<double*>(stw + N);
   const Geom& g = f.g;
   const int hs = g.hs;
   const int zs = g.ny * hs;
@@ -456,9 +463,14 @@ __device__ __forceinline__ void ct_zK_body(const FftPair& f, int bx, int ky, int
   const double* __restrict__ lamz = f.lam[2];
   for (int e = threadIdx.x; e < N; e += blockDim.x) {
     stw[e] = tw[e];
-    saz[e] = (float)(f.alpha * lamz[e]);
+    if (SYM64)
+      slz[e] = lamz[e];
+    else
+      saz[e] = (float)(f.alpha * lamz[e]);
   }
-  if (threadIdx.x < kCT) {
+  const int kxc = bx * kCT + c;
+  const double lxy = SYM64 ? f.lam[0][kxc < g.hx ? kxc : 0] + f.lam[1][ky] : 0.0;
+  if (!SYM64 && threadIdx.x < kCT) {
     const int kx = bx * kCT + (int)threadIdx.x;
     scxy[threadIdx.x] = (float)(f.gamma + f.alpha * (f.lam[0][kx < g.hx ? kx : 0] + f.lam[1][ky]));
   }
@@ -481,12 +493,18 @@ __device__ __forceinline__ void ct_zK_body(const FftPair& f, int bx, int ky, int
 #pragma unroll
     for (int p = 0; p < N1; ++p) w[p] = sx[c * LS + p + N1 * t];
     dft::dft<N1>(w);
-    const float inv_n = (float)(1.0 / ((double)g.nx * (double)g.ny * (double)g.nz));
-    const float cxy = scxy[c];
+    const double inv_n = 1.0 / ((double)g.nx * (double)g.ny * (double)g.nz);
+    const float cxy = SYM64 ? 0.f : scxy[c];
 #pragma unroll
     for (int k = 0; k < N1; ++k) {
-      const float d = cxy + saz[t + N2 * k];
-      const float kh = inv_n * __builtin_amdgcn_rcpf(d * d);
+      float kh;
+      if (SYM64) {
+        const double lam = f.alpha * (lxy + slz[t + N2 * k]) + f.gamma;
+        kh = (float)(inv_n / (lam * lam));
+      } else {
+        const float d = cxy + saz[t + N2 * k];
+        kh = (float)inv_n * __builtin_amdgcn_rcpf(d * d);
+      }
       w[k] = make_float2(w[k].x * kh, -w[k].y * kh);          // conj(K_hat X / |P|)
     }
     dft::dft<N1>(w);
@@ -516,14 +534,14 @@ __global__ __launch_bounds__(kCT * (N1 > N2 ? N1 : N2)) void k_fftc_y(FftPair f)
 }
 
 // XCD-aware tile order as in k_fft_z_K.
-template <int N1, int N2>
+template <int N1, int N2, bool SYM64>
 __global__ __launch_bounds__(kCT * (N1 > N2 ? N1 : N2)) void k_fftc_zK(FftPair f) {
   if (!gate(f.st, f.need_mode)) return;
   const uint32_t total = gridDim.x;
   uint32_t t = blockIdx.x;
   if ((total % kXCD) == 0) t = (t % kXCD) * (total / kXCD) + t / kXCD;
   const int bx = (int)(t % (uint32_t)f.nbx_z), r = (int)(t / (uint32_t)f.nbx_z);
-  ct_zK_body<N1, N2>(f, bx, r % f.g.ny, r / f.g.ny);
+  ct_zK_body<N1, N2, SYM64>(f, bx, r % f.g.ny, r / f.g.ny);
 }
 
 // The compile-time body for this problem's length, if it has one (batched
@@ -546,7 +564,7 @@ __device__ __forceinline__ bool ct_zK_dispatch(const FftPair& f, int bx, int ky,
   switch (f.g.nz) {
 #define LDDMM_CT_CASE(N, A, B)          \
   case N:                               \
-    ct_zK_body<A, B>(f, bx, ky, comp); \
+    ct_zK_body<A, B, false>(f, bx, ky, comp); \
     return true;
     LDDMM_CT_PLANS(LDDMM_CT_CASE)
 #undef LDDMM_CT_CASE
@@ -1746,21 +1764,25 @@ void launch_fft_y(const FftPair& f, const FftLaunch& L, int inverse, hipStream_t
 void launch_fft_z_K(const FftPair& f, const FftLaunch& L, hipStream_t s) {
   const dim3 grid(f.nbx_z * f.g.ny * 3);
   switch (f.g.nz) {
-#define LDDMM_CT_CASE(N, A, B)                                                               \
-  case N:                                                                                    \
-    hipLaunchKernelGGL((k_fftc_zK<A, B>), grid, dim3(kCT * (A > B ? A : B)), L.z_lds, s, f); \
+#define LDDMM_CT_CASE(N, A, B, SYM64)                                                              \
+  case N:                                                                                         \
+    hipLaunchKernelGGL((k_fftc_zK<A, B, SYM64>), grid, dim3(kCT * (A > B ? A : B)), L.z_lds, s, f); \
     return;
-    LDDMM_CT_PLANS(LDDMM_CT_CASE)
+#define LDDMM_CT_CASE32(N, A, B) LDDMM_CT_CASE(N, A, B, false)
+#define LDDMM_CT_CASE64(N, A, B) LDDMM_CT_CASE(N, A, B, true)
+    LDDMM_CT_PLANS(LDDMM_CT_CASE32)
     default:
       break;
   }
   if (f.alone) {
     switch (f.g.nz) {
-      LDDMM_CT_WIDE(LDDMM_CT_CASE)
+      LDDMM_CT_WIDE(LDDMM_CT_CASE64)
       default:
         break;
     }
   }
+#undef LDDMM_CT_CASE32
+#undef LDDMM_CT_CASE64
 #undef LDDMM_CT_CASE
   EMAX_SWITCH(L.ez,
     hipLaunchKernelGGL(k_fft_z_K<8>, grid, dim3(kBlock), L.z_lds, s, f),
