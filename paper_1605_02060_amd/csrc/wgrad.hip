@@ -32,6 +32,7 @@ namespace {
 
 constexpr int kBlk = 256;          // 4 wavefronts
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 constexpr uint32_t kOut = 0xfffffff0u;   // past every operand (at most 0xffff0000 bytes)
@@ -95,7 +96,9 @@ __device__ __forceinline__ bf16x8 frag(const char* lo, const char* hi) {
 }
 
 // DYV: dy rows are whole 16-byte units (M a multiple of 8), else staged value by value.
-template <int CB, int S, int MT, int WM, int KZ, bool DYV>
+// RAGGED: some chunk reaches past the output (an extent not a multiple of 2 x 8 x 8): four more
+// operations a fragment (decoder at 4 x 23^3 92 -> 110 us, head 53 -> 57), so a variant of its own.
+template <int CB, int S, int MT, int WM, int KZ, bool DYV, bool RAGGED>
 __global__ __launch_bounds__(kBlk) void k_wgrad(WgradArgs a) {
   using G = WgradGeom<CB, S, MT, WM, KZ>;
   constexpr int WK = 4 / WM, KST = 4 / WK;                   // k-steps per wavefront and chunk
@@ -205,7 +208,10 @@ __global__ __launch_bounds__(kBlk) void k_wgrad(WgradArgs a) {
   const bf16x8 ones = __builtin_bit_cast(bf16x8, one8);
   const bool bias = a.bias && kz0 == 0 && c0 == 0;
 
-  // k = 8 g + 4 h + r of a k-step is the voxel (plane, row 4 half + g, column 4 h + r)
+  // k = 8 g + 4 h + r of a k-step is the voxel (plane, row 4 half + g, column 4 h + r).  Voxels of
+  // a ragged chunk that lie past the output have zero dy, but their x may be real voxels of the
+  // last plane, row or column, which would enter taps that do not use them as 0 * inf: RAGGED
+  // clears their x.
   const int ch0 = split * a.per, ch1 = ch0 + a.per < a.nchunks ? ch0 + a.per : a.nchunks;
   if (ch0 < ch1) stage(ch0, 0);
   for (int ch = ch0; ch < ch1; ++ch) {
@@ -215,10 +221,26 @@ __global__ __launch_bounds__(kBlk) void k_wgrad(WgradArgs a) {
     if (ch + 1 < ch1) stage(ch + 1, buf ^ 1);
     const char* xb = lds + buf * G::STAGE;
     const char* db = xb + G::XB * (G::C2 ? 2 : 1);
+    int planes = 0, rows = 0;                                // of the chunk inside the output, or more
+    u32x4 cols = {0u, 0u, 0u, 0u};                           // mask of its columns
+    if constexpr (RAGGED) {
+      const int cx = ch % a.ncx, t = ch / a.ncx, cy = t % a.ncy, cz = t / a.ncy % a.ncz;
+      planes = a.od - 2 * cz;
+      rows = a.oh - 8 * cy;
+      const int n = a.ow - 8 * cx;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        cols[e] = (2 * e < n ? 0xffffu : 0u) | (2 * e + 1 < n ? 0xffff0000u : 0u);
+    }
 #pragma unroll
     for (int s = 0; s < KST; ++s) {
       const int ks = wk * KST + s, vz = ks >> 1, vy = (ks & 1) * 4 + g;
       const char* dp = db + ((vz * 8 + vy) * 8 + r) * G::DS + (wm * MT * 16 + 4 * q) * 2;
+      const u32x4 keep = vz < planes && vy < rows ? cols : u32x4{0u, 0u, 0u, 0u};
+      auto frag_x = [&](const char* lo, const char* hi) {
+        const bf16x8 f = frag(lo, hi);
+        return RAGGED ? __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, f) & keep) : f;
+      };
       bf16x8 fa[MT];
 #pragma unroll
       for (int i = 0; i < MT; ++i) fa[i] = frag(dp + i * 32, dp + 4 * G::DS + i * 32);
@@ -229,7 +251,7 @@ __global__ __launch_bounds__(kBlk) void k_wgrad(WgradArgs a) {
 #pragma unroll
         for (int t = 0; t < G::NTL; ++t) {
           const char* p = xp + ((t / 3) * G::EY + t % 3) * G::EX * 4;
-          const bf16x8 fb = frag(p, p + 16);
+          const bf16x8 fb = frag_x(p, p + 16);
 #pragma unroll
           for (int i = 0; i < MT; ++i)
             acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb, acc[i][t], 0, 0, 0);
@@ -242,7 +264,7 @@ __global__ __launch_bounds__(kBlk) void k_wgrad(WgradArgs a) {
         for (int t = 0; t < G::NTL; ++t) {
           const int tap = t / PT, kz = tap / 9, ky = tap / 3 % 3, kx = tap % 3;
           const char* p = xp + ((kz * G::EY + ky) * G::EX + kx) * G::XS + (t % PT) * 32;
-          const bf16x8 fb = frag(p, p + 4 * S * G::XS);
+          const bf16x8 fb = frag_x(p, p + 4 * S * G::XS);
 #pragma unroll
           for (int i = 0; i < MT; ++i)
             acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb, acc[i][t], 0, 0, 0);
@@ -343,10 +365,12 @@ int launch_one(WgradArgs a, long max_split, int target, hipStream_t s) {
   a.per = (int)((a.nchunks + ns - 1) / ns);
   a.nsplit = (int)ns;                            // trailing splits may be empty: they write zeros
   const dim3 grid(a.nsplit, ny);
-  if (a.M % 8 == 0)
-    hipLaunchKernelGGL((k_wgrad<CB, S, MT, WM, KZ, true>), grid, dim3(kBlk), G::LDS, s, a);
-  else
-    hipLaunchKernelGGL((k_wgrad<CB, S, MT, WM, KZ, false>), grid, dim3(kBlk), G::LDS, s, a);
+  const bool ragged = a.od % 2 || a.oh % 8 || a.ow % 8;
+  auto kernel = a.M % 8 == 0 ? (ragged ? k_wgrad<CB, S, MT, WM, KZ, true, true>
+                                       : k_wgrad<CB, S, MT, WM, KZ, true, false>)
+                             : (ragged ? k_wgrad<CB, S, MT, WM, KZ, false, true>
+                                       : k_wgrad<CB, S, MT, WM, KZ, false, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(kBlk), G::LDS, s, a);
   return a.nsplit;
 }
 
