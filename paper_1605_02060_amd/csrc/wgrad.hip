@@ -359,11 +359,15 @@ int launch_one(WgradArgs a, long max_split, int target, hipStream_t s) {
   a.ncb = a.ci / CB;
   const int ny = a.nkz * a.ncb * ((a.M + G::RB - 1) / G::RB);
   // Splits: a multiple of 8 where there are that many, so that the column blocks of a split run
-  // on one XCD and read its chunks behind one L2.
-  long ns = std::min<long>({std::max(1, target / ny), max_split, (long)a.nchunks});
-  if (ns > 8) ns = ns / 8 * 8;
-  a.per = (int)((a.nchunks + ns - 1) / ns);
-  a.nsplit = (int)ns;                            // trailing splits may be empty: they write zeros
+  // on one XCD and read its chunks behind one L2; but not where that leaves splits without a
+  // chunk and makes the others longer.  At most 7 are empty (they write zeros).
+  auto chunks_per = [&](long n) { return (a.nchunks + n - 1) / n; };
+  const long most = std::min<long>({std::max(1, target / ny), max_split, (long)a.nchunks});
+  long ns = most > 8 ? most / 8 * 8 : most;
+  if ((ns - 1) * chunks_per(ns) >= a.nchunks && chunks_per(most) < chunks_per(ns)) ns = most;
+  a.per = (int)chunks_per(ns);
+  const long busy = chunks_per(a.per);
+  a.nsplit = (int)std::min(ns, busy > 8 ? (busy + 7) / 8 * 8 : busy);
   const dim3 grid(a.nsplit, ny);
   const bool ragged = a.od % 2 || a.oh % 8 || a.ow % 8;
   auto kernel = a.M % 8 == 0 ? (ragged ? k_wgrad<CB, S, MT, WM, KZ, true, true>
