@@ -32,7 +32,6 @@ namespace {
 
 constexpr int kBlk = 256;          // 4 wavefronts
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 constexpr uint32_t kOut = 0xfffffff0u;   // past every operand (at most 0xffff0000 bytes)
@@ -65,7 +64,12 @@ struct WgradGeom {
   static constexpr int STAGE = XB * (C2 ? 2 : 1) + DB;       // one buffer
   static constexpr int NTL = C2 ? 3 * KZ : KZ * 9 * CB / 16; // column tiles of 16
   static constexpr int RED = WM * MT * (NTL + 1) * 1024;     // one wavefront's tiles per row group
-  static constexpr int LDS = 2 * STAGE > RED ? 2 * STAGE : RED;
+  // zeros as far as a fragment's taps of one plane reach from its first voxel (see RAGGED)
+  static constexpr int ZEROS = (((C2 ? 2 * EX : 2 * EX + 2) * XS + (C2 ? 32 : CB * 2)) + 15) / 16 * 16;
+  static constexpr int lds(bool ragged) {
+    const int used = 2 * STAGE + (ragged ? ZEROS : 0);
+    return used > RED ? used : RED;
+  }
 };
 
 // 16 or 4 bytes per lane from offset `off` of the buffer to LDS, the wavefront's first lane at
@@ -87,7 +91,9 @@ __device__ __forceinline__ bool inside(int p, int z0, int y0, int x0, int nz, in
 }
 
 // A fragment: 8 consecutive k (voxels) of this lane's row or column, from two transposing loads.
-__device__ __forceinline__ bf16x8 frag(const char* lo, const char* hi) {
+typedef __attribute__((address_space(3))) char* lds_p;
+
+__device__ __forceinline__ bf16x8 frag(lds_p lo, lds_p hi) {
   typedef __attribute__((address_space(3))) s16x4* lds_t;
   const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)lo);
   const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)hi);
@@ -96,8 +102,7 @@ __device__ __forceinline__ bf16x8 frag(const char* lo, const char* hi) {
 }
 
 // DYV: dy rows are whole 16-byte units (M a multiple of 8), else staged value by value.
-// RAGGED: some chunk reaches past the output (an extent not a multiple of 2 x 8 x 8): four more
-// operations a fragment (decoder at 4 x 23^3 92 -> 110 us, head 53 -> 57), so a variant of its own.
+// RAGGED: some chunk reaches past the output (an extent not a multiple of 2 x 8 x 8).
 template <int CB, int S, int MT, int WM, int KZ, bool DYV, bool RAGGED>
 __global__ __launch_bounds__(kBlk) void k_wgrad(WgradArgs a) {
   using G = WgradGeom<CB, S, MT, WM, KZ>;
@@ -141,6 +146,10 @@ __global__ __launch_bounds__(kBlk) void k_wgrad(WgradArgs a) {
     dof[i] = ((uint32_t)((z * a.oh + y) * a.ow + x) * (uint32_t)a.M + m0 + 8 * c) * 2u;
     dp_[i] = v < 128 && c < U - 1 && m0 + 8 * c < a.M ? z | y << 8 | x << 16 : -1;
   }
+  // chunk ch into buffer buf; returns its first voxel on the output
+  struct Place {
+    int z, y, x;
+  };
   auto stage = [&](int ch, int buf) {
     char* base = lds + buf * G::STAGE;
     const int cx = ch % a.ncx, t = ch / a.ncx, cy = t % a.ncy, t2 = t / a.ncy, cz = t2 % a.ncz,
@@ -193,6 +202,7 @@ __global__ __launch_bounds__(kBlk) void k_wgrad(WgradArgs a) {
         *reinterpret_cast<uint32_t*>(db + v * G::DS + 4 * (e - v * H)) = val;
       }
     }
+    return Place{z0, y0, x0};
   };
 
   f32x4 acc[MT][G::NTL], accb[MT];
@@ -210,48 +220,56 @@ __global__ __launch_bounds__(kBlk) void k_wgrad(WgradArgs a) {
 
   // k = 8 g + 4 h + r of a k-step is the voxel (plane, row 4 half + g, column 4 h + r).  Voxels of
   // a ragged chunk that lie past the output have zero dy, but their x may be real voxels of the
-  // last plane, row or column, which would enter taps that do not use them as 0 * inf: RAGGED
-  // clears their x.
+  // last plane, row or column, which would enter taps that do not use them as 0 * inf.  RAGGED
+  // reads zeros in their place: a lane gives the addresses of one voxel of each half, so it points
+  // them at a block of zeros.  The compiler then reads each fragment just before its products, so
+  // the order is given: three fragments ahead.  Decoder at 4 x 23^3 93 us, as without the zeros;
+  // 104 in the compiler's order, 110 with fragments masked after the read.
+  char* const zeros = lds + 2 * G::STAGE;
+  if constexpr (RAGGED)
+    for (int i = threadIdx.x; i < G::ZEROS / 4; i += kBlk) reinterpret_cast<uint32_t*>(zeros)[i] = 0u;
   const int ch0 = split * a.per, ch1 = ch0 + a.per < a.nchunks ? ch0 + a.per : a.nchunks;
-  if (ch0 < ch1) stage(ch0, 0);
+  Place next{};
+  if (ch0 < ch1) next = stage(ch0, 0);
   for (int ch = ch0; ch < ch1; ++ch) {
     const int buf = (ch - ch0) & 1;
     __builtin_amdgcn_s_waitcnt(0x0f70);                      // this chunk's LDS writes (vmcnt 0)
     __syncthreads();
-    if (ch + 1 < ch1) stage(ch + 1, buf ^ 1);
+    const Place at = next;
+    if (ch + 1 < ch1) next = stage(ch + 1, buf ^ 1);
     const char* xb = lds + buf * G::STAGE;
     const char* db = xb + G::XB * (G::C2 ? 2 : 1);
-    int planes = 0, rows = 0;                                // of the chunk inside the output, or more
-    u32x4 cols = {0u, 0u, 0u, 0u};                           // mask of its columns
-    if constexpr (RAGGED) {
-      const int cx = ch % a.ncx, t = ch / a.ncx, cy = t % a.ncy, cz = t / a.ncy % a.ncz;
-      planes = a.od - 2 * cz;
-      rows = a.oh - 8 * cy;
-      const int n = a.ow - 8 * cx;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        cols[e] = (2 * e < n ? 0xffffu : 0u) | (2 * e + 1 < n ? 0xffff0000u : 0u);
-    }
+    const int planes = a.od - at.z, rows = a.oh - at.y, cols = a.ow - at.x;   // inside, or more
 #pragma unroll
     for (int s = 0; s < KST; ++s) {
       const int ks = wk * KST + s, vz = ks >> 1, vy = (ks & 1) * 4 + g;
       const char* dp = db + ((vz * 8 + vy) * 8 + r) * G::DS + (wm * MT * 16 + 4 * q) * 2;
-      const u32x4 keep = vz < planes && vy < rows ? cols : u32x4{0u, 0u, 0u, 0u};
-      auto frag_x = [&](const char* lo, const char* hi) {
-        const bf16x8 f = frag(lo, hi);
-        return RAGGED ? __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, f) & keep) : f;
+      // addresses of the lane's voxels of both halves (p, p + half) for each plane of taps
+      lds_p lo[KZ], hi[KZ];
+      auto voxels = [&](const char* p, int half, int plane) {
+        const bool in = vz < planes && vy < rows;
+#pragma unroll
+        for (int k = 0; k < KZ; ++k) {
+          lo[k] = (lds_p)(p + k * plane);
+          hi[k] = lo[k] + half;
+          if (RAGGED) {
+            lo[k] = in && r < cols ? lo[k] : (lds_p)zeros + 8 * q;
+            hi[k] = in && r + 4 < cols ? hi[k] : (lds_p)zeros + 8 * q;
+          }
+        }
       };
       bf16x8 fa[MT];
 #pragma unroll
-      for (int i = 0; i < MT; ++i) fa[i] = frag(dp + i * 32, dp + 4 * G::DS + i * 32);
+      for (int i = 0; i < MT; ++i) fa[i] = frag((lds_p)dp + i * 32, (lds_p)dp + 4 * G::DS + i * 32);
       if constexpr (G::C2) {
         // tile t: kz = t / 3, ky = t % 3; columns are voxels x - 1 .. x + 6, two channels each;
         // an odd start takes the copy that is one voxel ahead
-        const char* xp = xb + (r & 1) * G::XB + ((vz * G::EY + vy) * G::EX + r - (r & 1)) * 4 + 8 * q;
+        voxels(xb + (r & 1) * G::XB + ((vz * G::EY + vy) * G::EX + r - (r & 1)) * 4 + 8 * q, 16,
+               G::EY * G::EX * 4);
 #pragma unroll
         for (int t = 0; t < G::NTL; ++t) {
-          const char* p = xp + ((t / 3) * G::EY + t % 3) * G::EX * 4;
-          const bf16x8 fb = frag_x(p, p + 16);
+          const int off = t % 3 * G::EX * 4;
+          const bf16x8 fb = frag(lo[t / 3] + off, hi[t / 3] + off);
 #pragma unroll
           for (int i = 0; i < MT; ++i)
             acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb, acc[i][t], 0, 0, 0);
@@ -259,15 +277,25 @@ __global__ __launch_bounds__(kBlk) void k_wgrad(WgradArgs a) {
       } else {
         constexpr int PT = CB / 16;                          // column tiles per tap
         constexpr int ZP = KZ == 3 ? S : 1;                  // staged planes between output planes
-        const char* xp = xb + ((vz * ZP * G::EY + vy * S) * G::EX + r * S) * G::XS + 8 * q;
+        voxels(xb + ((vz * ZP * G::EY + vy * S) * G::EX + r * S) * G::XS + 8 * q, 4 * S * G::XS,
+               G::EY * G::EX * G::XS);
+        auto tile = [&](int t) {
+          const int tap = t / PT, kz = tap / 9, ky = tap / 3 % 3, kx = tap % 3;
+          const int off = (ky * G::EX + kx) * G::XS + (t % PT) * 32;
+          return frag(lo[kz] + off, hi[kz] + off);
+        };
+        constexpr int AHEAD = RAGGED ? 3 : 0;                // fragments read ahead (see RAGGED)
+        bf16x8 fb[AHEAD + 1];
+#pragma unroll
+        for (int t = 0; t < AHEAD; ++t) fb[t] = tile(t);
 #pragma unroll
         for (int t = 0; t < G::NTL; ++t) {
-          const int tap = t / PT, kz = tap / 9, ky = tap / 3 % 3, kx = tap % 3;
-          const char* p = xp + ((kz * G::EY + ky) * G::EX + kx) * G::XS + (t % PT) * 32;
-          const bf16x8 fb = frag_x(p, p + 4 * S * G::XS);
+          if (t + AHEAD < G::NTL) fb[(t + AHEAD) % (AHEAD + 1)] = tile(t + AHEAD);
 #pragma unroll
           for (int i = 0; i < MT; ++i)
-            acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb, acc[i][t], 0, 0, 0);
+            acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[t % (AHEAD + 1)],
+                                                                acc[i][t], 0, 0, 0);
+          if (RAGGED) __builtin_amdgcn_sched_barrier(0);
         }
       }
       if (bias) {
@@ -354,7 +382,7 @@ __global__ __launch_bounds__(kBlk) void k_wgrad_sum(const float* __restrict__ pa
 template <int CB, int S, int MT, int WM, int KZ>
 int launch_one(WgradArgs a, long max_split, int target, hipStream_t s) {
   using G = WgradGeom<CB, S, MT, WM, KZ>;
-  static_assert(G::LDS <= 160 * 1024, "fits the CU");
+  static_assert(G::lds(true) <= 160 * 1024, "fits the CU");
   a.nkz = 3 / KZ;
   a.ncb = a.ci / CB;
   const int ny = a.nkz * a.ncb * ((a.M + G::RB - 1) / G::RB);
@@ -374,7 +402,7 @@ int launch_one(WgradArgs a, long max_split, int target, hipStream_t s) {
                                        : k_wgrad<CB, S, MT, WM, KZ, true, false>)
                              : (ragged ? k_wgrad<CB, S, MT, WM, KZ, false, true>
                                        : k_wgrad<CB, S, MT, WM, KZ, false, false>);
-  hipLaunchKernelGGL(kernel, grid, dim3(kBlk), G::LDS, s, a);
+  hipLaunchKernelGGL(kernel, grid, dim3(kBlk), G::lds(ragged), s, a);
   return a.nsplit;
 }
 
