@@ -989,7 +989,10 @@ bool launch_conv_frag(int op, const ConvArgs& a, hipStream_t s) {
   f.vec = f.M % 4 == 0 && ((uintptr_t)a.out & (a.out_f32 ? 15 : 7)) == 0 &&
           ((uintptr_t)a.mask & 7) == 0 &&
           (!a.add || (((uintptr_t)a.add & 7) == 0 && a.add_stride % 4 == 0 && a.add_off % 4 == 0));
-  if ((km == KM_32 || f.C == 2) && launch_halo(f, dg, a.s, a.n, s)) return true;
+  // The staged kernel loads 16 bytes a lane straight to LDS and wants them aligned, as the weight
+  // gradient does; k_conv_two's words and the fragments' buffer loads need 4-byte alignment.
+  const bool staged = f.C == 2 || (km == KM_32 && ((uintptr_t)a.x & 15) == 0);
+  if (staged && launch_halo(f, dg, a.s, a.n, s)) return true;
   const int mt = f.M <= 16 ? 1 : (f.M <= 32 ? 2 : (f.M <= 64 ? 4 : (f.M % 96 == 0 ? 6 : 8)));
   if (dg && a.s == 2) {
     Problem p{};
