@@ -102,15 +102,15 @@ __global__ __launch_bounds__(kBlock) void k_ubar_init(GradArgs a) {
 // to 32 us with 1024.  NaN components are passed over, as fmaxf does.
 constexpr unsigned kMaxParts = 2 * kPartMax;   // floats in one step's worth of min-det partials
 
-__global__ __launch_bounds__(kBlock) void k_Lv(GradArgs a) {
+__device__ __forceinline__ void Lv_body(const GradArgs& a, const float* v, uint32_t nblocks) {
   const Geom g = a.g;
   const long long N = g.n;
   const uint32_t n = (uint32_t)N;
   const float c2 = a.alpha * g.inv_h * g.inv_h;
   float m = 0.f;
   for (int c = 0; c < 3; ++c) {
-    const rsrc_t V = rsrc(a.v + c * N, n), W = rsrc(a.w + c * N, n);
-    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+    const rsrc_t V = rsrc(v + c * N, n), W = rsrc(a.w + c * N, n);
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += nblocks * kBlock) {
       int x, y, z;
       vcoord(g, i, x, y, z);
       const Nbr nb = periodic_nbr(g, i, x, y, z);
@@ -128,6 +128,8 @@ __global__ __launch_bounds__(kBlock) void k_Lv(GradArgs a) {
     a.vpart[blockIdx.x] = m;
   }
 }
+
+__global__ __launch_bounds__(kBlock) void k_Lv(GradArgs a) { Lv_body(a, a.v, gridDim.x); }
 
 // Splat radius: floor(max_x max_axis |dt v_j / h|) + 1 (at least one source
 // further than any displacement reaches).
@@ -200,6 +202,11 @@ __global__ __launch_bounds__(kBlock) void k_coord_grad(GradArgs a) {
 // are those of the general body, which larger reaches run.  The general body
 // spent its time on address and cell arithmetic (27 x about 30 instructions per
 // output): 91.2 us at 128^3 against 54.9 us staged.
+// Below kStagedVoxels it runs all reaches: its blocks then fill the chip at once, where the staged
+// one's few march with one memory latency per plane (35 us a step at 32^3 against 13).  Whole call,
+// T = 10, staged against general: 32^3 488 and 239 us, 64^3 554 and 363, 80^3 691 and 647,
+// 96^3 839 and 920, 112^3 1171 and 1462.
+constexpr long long kStagedVoxels = 655360;
 constexpr int kSX = 64, kSY = 4;
 constexpr int kSXH = kSX + 2, kSYH = kSY + 2;
 constexpr int kSPlane = kSXH * kSYH;
@@ -402,24 +409,26 @@ __device__ __forceinline__ void splat_staged(const GradArgs& a, uint32_t block, 
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_splat(GradArgs a) {
+__global__ __launch_bounds__(kBlock) void k_splat_staged(GradArgs a) {
+  if (splat_radius(a) == 1) splat_staged(a, blockIdx.x, gridDim.x);   // uniform over the grid
+}
+
+// Any reach: each output looks at every source within it.
+__device__ __forceinline__ void splat_any(const GradArgs& a, uint32_t block, uint32_t nblocks) {
   const Geom g = a.g;
   const long long N = g.n;
   const uint32_t n = (uint32_t)N;
   int Rr = splat_radius(a);
-  if (Rr == 1 && 3LL * N < (1LL << 30)) {      // uniform over the grid; byte offsets of 3 n floats
-    splat_staged(a, blockIdx.x, gridDim.x);
-    return;
-  }
+  if (Rr == 1 && a.staged) return;
   const rsrc_t V0 = rsrc(a.v, n), V1 = rsrc(a.v + N, n), V2 = rsrc(a.v + 2 * N, n);
   const rsrc_t B0 = rsrc(a.ub_in, n), B1 = rsrc(a.ub_in + N, n), B2 = rsrc(a.ub_in + 2 * N, n);
   const rsrc_t O0 = rsrc(a.ub_out, n), O1 = rsrc(a.ub_out + N, n), O2 = rsrc(a.ub_out + 2 * N, n);
   if (Rr > kSplatMaxR) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *a.overflow = 1;
+    if (block == 0 && threadIdx.x == 0) *a.overflow = 1;
     Rr = kSplatMaxR;
   }
   const float dt = a.dt, ih = g.inv_h;
-  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+  for (uint32_t i = block * kBlock + threadIdx.x; i < n; i += nblocks * kBlock) {
     int zx, zy, zz;
     vcoord(g, i, zx, zy, zz);
     float s0 = 0.f, s1 = 0.f, s2 = 0.f;
@@ -453,6 +462,20 @@ __global__ __launch_bounds__(kBlock) void k_splat(GradArgs a) {
   }
 }
 
+// The splat of a step where k_splat_staged does not run or finds a larger reach, and the L v
+// pass of the step before it (v_prev, on the first a.nvpart blocks): neither needs the other, and
+// where the splat returns at once its launch costs nothing.  The general body needs a grid and
+// an occupancy of its own: in one kernel with the staged one (its few blocks, 33 KB of LDS) energy
+// and gradient at T = 10 and 1.5 voxels a step took 1196 us at 32^3, 2195 at 64^3 and 5184 at
+// 128^3; 458, 782 and 4562 now.
+__global__ __launch_bounds__(kBlock) void k_splat_Lv(GradArgs a, const float* v_prev) {
+  const uint32_t nlv = v_prev ? (uint32_t)a.nvpart : 0u;
+  if (blockIdx.x < nlv)
+    Lv_body(a, v_prev, nlv);
+  else
+    splat_any(a, blockIdx.x - nlv, gridDim.x - nlv);
+}
+
 // ------------------------------------------------------------ launchers
 
 void launch_ubar_init(const GradArgs& a, hipStream_t s) {
@@ -462,17 +485,32 @@ void launch_ubar_init(const GradArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(k_ubar_init<1>, dim3(grid_for(a.g.n)), dim3(kBlock), 0, s, a);
 }
 
-void launch_grad_step(const GradArgs& a0, hipStream_t s) {
+static unsigned Lv_blocks(const Geom& g) {
+  const unsigned gb = grid_for(g.n);
+  return gb < kMaxParts ? gb : kMaxParts;
+}
+
+void launch_Lv(const GradArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(k_Lv, dim3(Lv_blocks(a.g)), dim3(kBlock), 0, s, a);
+}
+
+// Blocks of the general splat: every wavefront slot of the chip (1024: 1.4 times as long at 128^3);
+// where they return at once, 0.9 us a step.
+constexpr unsigned kSplatBlocks = 2048;
+
+void launch_grad_step(const GradArgs& a0, const float* v_prev, hipStream_t s) {
   GradArgs a = a0;
   const unsigned gb = grid_for(a.g.n);
-  const unsigned lb = gb < kMaxParts ? gb : kMaxParts;
-  a.nvpart = (int)lb;
-  hipLaunchKernelGGL(k_Lv, dim3(lb), dim3(kBlock), 0, s, a);
+  a.nvpart = (int)Lv_blocks(a.g);
+  a.staged = a.g.n >= kStagedVoxels && 3 * a.g.n < (1LL << 30);   // byte offsets of 3 n floats
   hipLaunchKernelGGL(k_coord_grad, dim3(gb), dim3(kBlock), 0, s, a);
-  // blocks for the staged body (the general one strides over any grid)
-  const SplatTiling t = splat_tiling(a.g);
-  const int tiles = (t.ntx * t.nty * t.nrun + kXCD - 1) / kXCD * kXCD;
-  hipLaunchKernelGGL(k_splat, dim3(tiles), dim3(kBlock), 0, s, a);
+  if (a.staged) {
+    const SplatTiling t = splat_tiling(a.g);
+    const int tiles = (t.ntx * t.nty * t.nrun + kXCD - 1) / kXCD * kXCD;
+    hipLaunchKernelGGL(k_splat_staged, dim3(tiles), dim3(kBlock), 0, s, a);
+  }
+  const unsigned sb = gb < kSplatBlocks ? gb : kSplatBlocks;
+  hipLaunchKernelGGL(k_splat_Lv, dim3((v_prev ? a.nvpart : 0) + sb), dim3(kBlock), 0, s, a, v_prev);
 }
 
 }  // namespace lddmm

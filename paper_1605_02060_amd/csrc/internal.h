@@ -298,11 +298,15 @@ struct GradArgs {
   float dt, alpha, gamma, reg;   // reg = 2 dt h^3
   float* vpart;          // device: max |v_j| per block of the L v pass, nvpart of them
   int nvpart;
+  int staged;            // steps of reach 1 run the staged splat
   float* vmax;           // device: max |v_j| of the step (sets the splat's reach)
   int* overflow;         // device flag: radius beyond the supported maximum
 };
 void launch_ubar_init(const GradArgs& a, hipStream_t s);
-void launch_grad_step(const GradArgs& a, hipStream_t s);
+void launch_Lv(const GradArgs& a, hipStream_t s);
+// One reverse step, after the L v pass of its velocity, with that of the step before it (v_prev,
+// or null at the first).
+void launch_grad_step(const GradArgs& a, const float* v_prev, hipStream_t s);
 
 // control.hip
 void launch_energy_out_checked(const State* st, const int* overflow, double* out4, hipStream_t s);

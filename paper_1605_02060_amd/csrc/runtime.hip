@@ -673,6 +673,8 @@ static void exact_gradient(Ctx& c, const float* v, float* grad, hipStream_t s) {
   a.u = c.u0 + (long long)sl[T] * 3 * n;
   a.ub_out = c.ub + (long long)(T & 1) * 3 * n;
   launch_ubar_init(a, s);
+  a.v = v + (long long)(T - 1) * 3 * n;
+  launch_Lv(a, s);
   int seg_lo = -1;   // first step of the segment whose interior is recomputed
   for (int j = T - 1; j >= 0; --j) {
     int uslot;
@@ -695,7 +697,7 @@ static void exact_gradient(Ctx& c, const float* v, float* grad, hipStream_t s) {
     a.ub_in = c.ub + (long long)((j + 1) & 1) * 3 * n;
     a.ub_out = c.ub + (long long)(j & 1) * 3 * n;
     a.grad = grad + (long long)j * 3 * n;
-    launch_grad_step(a, s);
+    launch_grad_step(a, j > 0 ? v + (long long)(j - 1) * 3 * n : nullptr, s);
   }
 }
 
