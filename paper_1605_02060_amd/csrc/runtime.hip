@@ -1301,7 +1301,9 @@ int lddmm_smooth(const int32_t P[3], double spacing, double alpha, double gamma,
   launch_level_begin(c.st, 1.0, 0, 0, s);
   level_tables(c, L, s);
   // the first pass reads b where it is; its 16-byte loads want it (and so every row and
-  // component, when 4 divides P[0]) on a 16-byte boundary
+  // component, when 4 divides P[0]) on a 16-byte boundary.  b and out may alias: of all the
+  // passes, fused or not, only the first (forward along x) reads b, and only the last (inverse
+  // along x) writes out, from the spectra.
   if (((uintptr_t)b & 15) == 0)
     c.b = const_cast<float*>(b);
   else
