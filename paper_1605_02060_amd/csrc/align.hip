@@ -21,6 +21,7 @@
 #include <cfloat>
 #include <cmath>
 
+#include "divide.h"
 #include "internal.h"
 #include "lddmm.h"
 
@@ -31,7 +32,6 @@ constexpr int kWaves = kBlock / 64;
 constexpr int kParts = 13;              // MSE sum, r g_d p_e (9), r g_d (3)
 constexpr int kAlignBlocksMax = 2048;
 constexpr int kControl = 64 * kParts;   // one wavefront per sum
-constexpr double kDivMax = 1e300;
 
 struct AlignGeom {
   int nx0, ny0, nz0;                    // template grid
@@ -126,20 +126,11 @@ __global__ void k_align_init(const double* __restrict__ S0, double step,
   }
 }
 
-// a / h, correctly rounded, with ih = 1 / h rounded: two corrections by the exact remainder
-// (the first makes the quotient faithful, the second then rounds it as the division does)
-// in 5 operations instead of the division's dozen; a not finite is left to the product.
-__device__ __forceinline__ double div_by(double a, double h, double ih) {
-  const double q0 = a * ih;
-  const double q1 = __builtin_fma(__builtin_fma(-q0, h, a), ih, q0);
-  const double q2 = __builtin_fma(__builtin_fma(-q1, h, a), ih, q1);
-  return fabs(a) < kDivMax ? q2 : q0;
-}
-
 // A thread walks zlen planes at one (x, y), kBlock consecutive (x, y) of a plane to a block, so
 // the position's x and y terms, and x and y in the gradient's sums, are left out of the walk:
 // bound by FP64 and FP32 arithmetic.  One voxel after the other through the flat index, with
 // divisions and 13 sums a voxel, took 101 us at 264 x 160 x 228: 59 us now.
+template <bool FITS>
 __global__ __launch_bounds__(kBlock) void k_align_partials(AlignGeom g, const float* __restrict__ I0,
                                                            const float* __restrict__ I1,
                                                            const AlignState* __restrict__ st,
@@ -183,9 +174,9 @@ __global__ __launch_bounds__(kBlock) void k_align_partials(AlignGeom g, const fl
         const double yz = g.h1 * zu;
         pz[u] = yz - g.yc[2];
         t[u] = I1[(uint32_t)zu * nxy + xy];
-        sample_grad(I0, g.nx0, g.ny0, g.nz0, div_by(q0 + B02 * yz + C0, g.h0, ih0),
-                    div_by(q1 + B12 * yz + C1, g.h0, ih0), div_by(q2 + B22 * yz + C2, g.h0, ih0),
-                    v[u], gx[u], gy[u], gz[u]);
+        sample_grad(I0, g.nx0, g.ny0, g.nz0, quotient<FITS>(q0 + B02 * yz + C0, g.h0, ih0),
+                    quotient<FITS>(q1 + B12 * yz + C1, g.h0, ih0),
+                    quotient<FITS>(q2 + B22 * yz + C2, g.h0, ih0), v[u], gx[u], gy[u], gz[u]);
       }
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
@@ -369,6 +360,7 @@ struct ApplyAffArgs {
   void* dst;
 };
 
+template <bool FITS>
 __global__ __launch_bounds__(kBlock) void k_apply_affine(ApplyAffArgs a) {
   const double B00 = a.S[0], B01 = a.S[1], B02 = a.S[2], C0 = a.S[3];
   const double B10 = a.S[4], B11 = a.S[5], B12 = a.S[6], C1 = a.S[7];
@@ -385,9 +377,9 @@ __global__ __launch_bounds__(kBlock) void k_apply_affine(ApplyAffArgs a) {
       yy += (double)a.u[a.n + i];
       yz += (double)a.u[2 * a.n + i];
     }
-    const double qx = div_by(B00 * yx + B01 * yy + B02 * yz + C0, a.hs, ihs);
-    const double qy = div_by(B10 * yx + B11 * yy + B12 * yz + C1, a.hs, ihs);
-    const double qz = div_by(B20 * yx + B21 * yy + B22 * yz + C2, a.hs, ihs);
+    const double qx = quotient<FITS>(B00 * yx + B01 * yy + B02 * yz + C0, a.hs, ihs);
+    const double qy = quotient<FITS>(B10 * yx + B11 * yy + B12 * yz + C1, a.hs, ihs);
+    const double qz = quotient<FITS>(B20 * yx + B21 * yy + B22 * yz + C2, a.hs, ihs);
     if (a.interp == LDDMM_INTERP_LINEAR) {
       float v, gx, gy, gz;
       sample_grad(static_cast<const float*>(a.src), a.snx, a.sny, a.snz, qx, qy, qz, v, gx, gy,
@@ -481,11 +473,12 @@ int lddmm_align(const lddmm_grid* template_grid, const float* template_image,
   hipStream_t s = (hipStream_t)stream;
   (void)hipGetLastError();   // clear an earlier error: the status returned is these launches'
   hipLaunchKernelGGL(k_align_init, dim3(1), dim3(64), 0, s, affine, params->step, st);
+  auto partials = div_by_fits(g.h0) ? k_align_partials<true> : k_align_partials<false>;
   for (int slot = 0; slot <= params->iters; ++slot) {
     {
       ProfScope ps(LDDMM_PROF_ALIGN, n1, s);
-      hipLaunchKernelGGL(k_align_partials, dim3(nblk), dim3(kBlock), 0, s, g, template_image,
-                         target_image, st, part);
+      hipLaunchKernelGGL(partials, dim3(nblk), dim3(kBlock), 0, s, g, template_image, target_image,
+                         st, part);
     }
     hipLaunchKernelGGL(k_align_control, dim3(1), dim3(kControl), 0, s, part, nblk, g, st,
                        (int)params->mode, slot, (int)params->max_halvings, trace);
@@ -523,8 +516,8 @@ int lddmm_apply_affine(const lddmm_grid* dst_grid, const float* u, const double*
   long long blocks = (nd + kBlock - 1) / kBlock;
   if (blocks > 8192) blocks = 8192;
   (void)hipGetLastError();   // clear an earlier error: the status returned is these launches'
-  hipLaunchKernelGGL(k_apply_affine, dim3((unsigned)blocks), dim3(kBlock), 0, (hipStream_t)stream,
-                     a);
+  hipLaunchKernelGGL(div_by_fits(a.hs) ? k_apply_affine<true> : k_apply_affine<false>,
+                     dim3((unsigned)blocks), dim3(kBlock), 0, (hipStream_t)stream, a);
   return launch_status();
 }
 
