@@ -173,6 +173,7 @@ __global__ __launch_bounds__(kBlock) void k_morph(MGrid g, const uint32_t* __res
     tab[k] = (int8_t)w;
   }
   __syncthreads();
+  const int my = min(m, g.ny - 1), mz = min(m, g.nz - 1);  // rows further off lie outside for all
   for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < g.nwords;
        i += (long long)gridDim.x * kBlock) {
     const uint32_t row = (uint32_t)i / (uint32_t)g.W;      // fewer than 2^25 words
@@ -180,16 +181,19 @@ __global__ __launch_bounds__(kBlock) void k_morph(MGrid g, const uint32_t* __res
     const int z = (int)(row / (uint32_t)g.ny), y = (int)(row - (uint32_t)z * g.ny);
     const uint32_t valid = valid_bits(g, wx), decided = DILATE ? valid : 0u;
     uint32_t acc = in[i];
-    for (int dz = -m; dz <= m && acc != decided; ++dz) {
+    // the ball's rows (0, +-m) and (+-m, 0) hold a voxel: an erosion leaves none where one of them
+    // lies outside the grid
+    if (!DILATE && (z < m || z + m >= g.nz || y < m || y + m >= g.ny)) acc = 0u;
+    for (int dz = -mz; dz <= mz && acc != decided; ++dz) {
       const int zz = z + dz;
       const bool zok = zz >= 0 && zz < g.nz;
-      for (int dy0 = -m; dy0 <= m; dy0 += kMorphAhead) {
+      for (int dy0 = -my; dy0 <= my; dy0 += kMorphAhead) {
         int w[kMorphAhead];
         uint32_t p[kMorphAhead], c[kMorphAhead], n[kMorphAhead];
 #pragma unroll
         for (int u = 0; u < kMorphAhead; ++u) {
           const int dy = dy0 + u, yy = y + dy;
-          w[u] = dy <= m ? __builtin_amdgcn_readfirstlane(tab[(dz + m) * side + dy + m]) : -1;
+          w[u] = dy <= my ? __builtin_amdgcn_readfirstlane(tab[(dz + m) * side + dy + m]) : -1;
           // rows outside the grid are background; their loads go to the word's own row
           const bool ok = w[u] >= 0 && zok && yy >= 0 && yy < g.ny;
           const uint32_t* rb = in + (ok ? ((long long)zz * g.ny + yy) * g.W + wx : i);
