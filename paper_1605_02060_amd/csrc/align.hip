@@ -38,8 +38,9 @@ struct AlignGeom {
   int nx1, ny1, nz1;                    // target grid
   long long n1;                         // < 2^30 (each axis at most LDDMM_MAX_DIM)
   FastDiv fx1;                          // division by nx1
-  int nxyb, nzc, zlen;                  // blocks of a plane, chunks of planes, planes in one
-  FastDiv fxyb;                         // division by nxyb
+  int nxyb, nzc, zlen;                  // blocks of a plane, chunks of planes, planes of a walk
+  int nsub;                             // walks side by side in a block, one chunk after the other
+  FastDiv fxyb, fxy;                    // division by nxyb, by the voxels of a plane
   double h0, h1;
   double yc[3];                         // target centre (physical)
   double rho2;                          // mean squared distance of target voxels from yc
@@ -129,8 +130,10 @@ __global__ void k_align_init(const double* __restrict__ S0, double step,
 // A thread walks zlen planes at one (x, y), kBlock consecutive (x, y) of a plane to a block, so
 // the position's x and y terms, and x and y in the gradient's sums, are left out of the walk:
 // bound by FP64 and FP32 arithmetic.  One voxel after the other through the flat index, with
-// divisions and 13 sums a voxel, took 101 us at 264 x 160 x 228: 59 us now.
-template <bool FITS>
+// divisions and 13 sums a voxel, took 101 us at 264 x 160 x 228: 59 us now.  THIN: walks over
+// planes of at most half a block go side by side (20 steps on 1000 planes of 8 x 8: 338 us, 581
+// with idle threads); a variant of its own, as the others would be 0.8 % slower.
+template <bool FITS, bool THIN>
 __global__ __launch_bounds__(kBlock) void k_align_partials(AlignGeom g, const float* __restrict__ I0,
                                                            const float* __restrict__ I1,
                                                            const AlignState* __restrict__ st,
@@ -152,10 +155,11 @@ __global__ __launch_bounds__(kBlock) void k_align_partials(AlignGeom g, const fl
   for (uint32_t task = (blockIdx.x % kXCD) * per + blockIdx.x / kXCD; task < tasks;
        task += gridDim.x) {
     const uint32_t zc = fdiv(task, g.fxyb), xyb = task - zc * (uint32_t)g.nxyb;
-    const uint32_t xy = xyb * kBlock + threadIdx.x;
-    if (xy >= nxy) continue;
+    const uint32_t sub = THIN ? fdiv(threadIdx.x, g.fxy) : 0u;
+    const uint32_t xy = THIN ? threadIdx.x - sub * nxy : xyb * kBlock + threadIdx.x;
+    if (THIN ? sub >= (uint32_t)g.nsub : xy >= nxy) continue;
     const uint32_t y = fdiv(xy, g.fx1), x = xy - y * (uint32_t)g.nx1;
-    const int z0 = (int)zc * g.zlen, z1 = z0 + g.zlen < g.nz1 ? z0 + g.zlen : g.nz1;
+    const int z0 = (int)(THIN ? zc * g.nsub + sub : zc) * g.zlen, z1 = z0 + g.zlen < g.nz1 ? z0 + g.zlen : g.nz1;
     // template index position (B y + c) / h0, in the definition's order of
     // operations (no multiply-add fusion in this file): positions that are
     // whole numbers stay whole, so the cell, and the one-sided derivative on
@@ -418,12 +422,15 @@ AlignGeom make_align_geom(const lddmm_grid* t0, const lddmm_grid* t1) {
   g.fx1 = make_fastdiv((uint32_t)t1->nx);
   g.nxyb = (t1->nx * t1->ny + kBlock - 1) / kBlock;
   g.fxyb = make_fastdiv((uint32_t)g.nxyb);
-  // as many chunks of planes as the blocks allow
-  g.nzc = align_blocks(g.n1) / g.nxyb;
-  if (g.nzc < 1) g.nzc = 1;
-  if (g.nzc > t1->nz) g.nzc = t1->nz;
-  g.zlen = (t1->nz + g.nzc - 1) / g.nzc;
-  g.nzc = (t1->nz + g.zlen - 1) / g.zlen;
+  const int nxy = t1->nx * t1->ny;
+  g.nsub = nxy <= kBlock ? kBlock / nxy : 1;
+  g.fxy = make_fastdiv((uint32_t)nxy);
+  // as many walks as the blocks allow
+  long long walks = (long long)(align_blocks(g.n1) / g.nxyb) * g.nsub;
+  if (walks < 1) walks = 1;
+  if (walks > t1->nz) walks = t1->nz;
+  g.zlen = (int)((t1->nz + walks - 1) / walks);
+  g.nzc = (t1->nz + g.zlen * g.nsub - 1) / (g.zlen * g.nsub);
   g.h0 = t0->spacing;
   g.h1 = t1->spacing;
   g.yc[0] = 0.5 * t1->spacing * (t1->nx - 1);
@@ -473,7 +480,9 @@ int lddmm_align(const lddmm_grid* template_grid, const float* template_image,
   hipStream_t s = (hipStream_t)stream;
   (void)hipGetLastError();   // clear an earlier error: the status returned is these launches'
   hipLaunchKernelGGL(k_align_init, dim3(1), dim3(64), 0, s, affine, params->step, st);
-  auto partials = div_by_fits(g.h0) ? k_align_partials<true> : k_align_partials<false>;
+  const bool fits = div_by_fits(g.h0);
+  auto partials = g.nsub > 1 ? (fits ? k_align_partials<true, true> : k_align_partials<false, true>)
+                             : (fits ? k_align_partials<true, false> : k_align_partials<false, false>);
   for (int slot = 0; slot <= params->iters; ++slot) {
     {
       ProfScope ps(LDDMM_PROF_ALIGN, n1, s);
