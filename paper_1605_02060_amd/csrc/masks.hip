@@ -381,20 +381,28 @@ __global__ __launch_bounds__(kBlock) void k_edt_xy(MGrid g, const uint32_t* __re
 
 // z pass at the voxels of one surface (its set bits only): d2 = min_z' g2(x, y, z') + (z -
 // z')^2, searched outward from z until (z - z')^2 >= d2; then the Hausdorff maximum and
-// the histogram of d2.  A wavefront spreads the set bits of its 64 words over its lanes
-// (a thread that walked its own word's bits one after the other left most lanes idle),
+// the histogram of d2.  A wavefront spreads the set bits of up to 64 words over its lanes
+// (a thread that walked its own word's bits one after the other left most lanes idle; a grid of few
+// words gives each wavefront fewer, down to kZFewest: both masks noise on 300 x 2 x 300, all calls
+// together, 76 us with 64 words each),
 // and each lane looks kZAhead planes each way ahead, so the search is not one memory
 // latency per plane.  Few large blocks: every block adds its counts to the same few
 // bins.  blockIdx.y: the direction, as above.
 constexpr int kZAhead = 4;
-constexpr int kZBlock = 1024, kZWaves = kZBlock / 64, kZBlocks = 128;
+constexpr int kZBlock = 1024, kZWaves = kZBlock / 64, kZBlocks = 128, kZFewest = 8;
+
+inline int z_words(long long nwords) {
+  int n = 64;
+  while (n > kZFewest && nwords < (long long)n * kZWaves * kZBlocks) n /= 2;
+  return n;
+}
 
 __global__ __launch_bounds__(kZBlock) void k_edt_z_collect(MGrid g, const uint32_t* __restrict__ sA,
                                                           const uint32_t* __restrict__ sB,
                                                           const uint32_t* __restrict__ gB,
                                                           const uint32_t* __restrict__ gA,
                                                           uint32_t* __restrict__ hist,
-                                                          uint32_t nbins,
+                                                          uint32_t nbins, int nw,
                                                           unsigned* __restrict__ scal) {
   __shared__ uint32_t lh[kLdsBins];
   __shared__ unsigned lmax, lcnt;
@@ -411,9 +419,9 @@ __global__ __launch_bounds__(kZBlock) void k_edt_z_collect(MGrid g, const uint32
   const long long plane = (long long)g.nx * g.ny;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   unsigned my_max = 0u, my_cnt = 0u;
-  for (long long w0 = ((long long)blockIdx.x * kZWaves + wv) * 64; w0 < g.nwords;
-       w0 += (long long)gridDim.x * kZBlock) {
-    const uint32_t mine = w0 + lane < g.nwords ? sa[w0 + lane] : 0u;
+  for (long long w0 = ((long long)blockIdx.x * kZWaves + wv) * nw; w0 < g.nwords;
+       w0 += (long long)gridDim.x * kZWaves * nw) {
+    const uint32_t mine = lane < nw && w0 + lane < g.nwords ? sa[w0 + lane] : 0u;
     unsigned end = __popc(mine);
     for (int o = 1; o < 64; o <<= 1) {
       const unsigned up = __shfl_up(end, o);
@@ -729,7 +737,8 @@ int lddmm_surface_distance(const lddmm_grid* grid, const float* mask_a, const fl
       hipLaunchKernelGGL(k_edt_xy, dim3((unsigned)(g.nz * g.W), 2), dim3(kBlock), edt_lds(g.ny), s,
                          g, a, b, g1, g2);
     }
-    hipLaunchKernelGGL(k_edt_z_collect, dim3(kZBlocks, 2), dim3(kZBlock), 0, s, g, a, b, g1, g2, hist, nbins, scal);
+    hipLaunchKernelGGL(k_edt_z_collect, dim3(kZBlocks, 2), dim3(kZBlock), 0, s, g, a, b, g1, g2, hist,
+                       nbins, z_words(g.nwords), scal);
     hipLaunchKernelGGL(k_tile_sums, dim3((nbins + kBlock - 1) / kBlock), dim3(kBlock), 0, s, hist,
                        nbins, tsum);
     hipLaunchKernelGGL(k_surface_final, dim3(1), dim3(kBlock), 0, s, hist, nbins, tsum, scal,
