@@ -301,9 +301,8 @@ def stored_traffic(kernel):
     return None if k is None else k["fetch_bytes"] + k["write_bytes"]
 
 
-# Calibration: the copy of the finest-level velocity buffer between pyramid levels
-# (k_copy of 3 T |P| floats; the bandwidth probe copies the same size) reads and
-# writes exactly this many bytes.
+# Calibration: the bandwidth probe's copy of the finest-level velocity (k_copy of
+# 3 T |P| floats) reads and writes exactly this many bytes.
 COPY_FLOATS = 3 * T * 280 * 160 * 240
 FINEST_VOXELS = 280 * 160 * 240
 
@@ -329,8 +328,7 @@ def compute_traffic(fetch_db, write_db, out_path):
     per = {}
     for tag, db, counter in (("fetch", fetch_db, "FETCH_SIZE"), ("write", write_db, "WRITE_SIZE")):
         rows = per_kernel(db, counter)
-        # the copies of v between pyramid levels share one launch shape: the
-        # finest-level copy is the group of the longest ones
+        # the probe's copies are the group of the longest ones
         allc = [(d, v) for (name, grid), items in rows.items() if name == "k_copy"
                 for d, v in items]
         if not allc:

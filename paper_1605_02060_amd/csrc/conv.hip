@@ -701,8 +701,8 @@ __global__ __launch_bounds__(kBlk) void k_conv_halo(HaloArgs a) {
 // The network's first layer.  A voxel's two channels are one 32-bit word, so a block stages the
 // words of a P2X x P2Y x P2Z tile and its halo in LDS and a fragment is four reads at offsets
 // that belong to the lane alone (the taps of its k-values), the tile's place an immediate; the 54
-// weights of a row stay in two registers' worth of fragments.  Bound by the writes (32 B per
-// voxel for 16 rows).  Read straight from memory (the fragment kernel: eight gathers of 4 B per
+// weights of a row stay in two registers' worth of fragments.  Bound by its vector instructions
+// (0.71 a cycle and CU at 8 x 96^3, where it writes 226 MB at 3.1 TB/s).  Read straight from memory (the fragment kernel: eight gathers of 4 B per
 // lane for 16 voxels, each as dear to L1 as one of 16 B) 8 x 96^3 took 180 us and one 29:
 // 70 and 15.5 now (93 and 19 with four planes to a block and stores of 8 B).
 // k order and instruction as there, so the same bits.

@@ -80,9 +80,9 @@ void launch_down2(const float* src, const Geom& fine, float* dst, const Geom& co
 // Cell-centred 2x trilinear upsample, coordinates clamped: fine i <-> coarse (i + 1/2)/2 - 1/2,
 // i.e. fine 2i and 2i + 1 lie 1/4 before and after coarse i.  A thread makes the 2 x 2 fine
 // voxels of one coarse column in one fine plane from 3 x 3 x 2 coarse values, and stores
-// pairs: bound by the 4 B it writes per fine voxel.  For a 10-step velocity of 96^3
-// (106 MB written) 40 us, where one voxel per thread with 64-bit divisions for its
-// place took 122.  With `st` the source is the iterate's buffer (a or b, by st->base)
+// pairs: bound by its vector instructions (0.95 of one a cycle and CU on large grids).  For a
+// 10-step velocity of 96^3 40 us (106 MB written and 59 read, 4 TB/s), where one voxel per
+// thread with 64-bit divisions for its place took 122.  With `st` the source is the iterate's buffer (a or b, by st->base)
 // and the destination the other one, so a level change copies nothing (two copies of
 // 1.29 GB before, 417 us each, at the finest atlas level).
 struct UpAxis {
@@ -1383,9 +1383,10 @@ void launch_crop3(const float* u, const Geom& g, int Nx, int Ny, int Nz, float* 
                      Nz, out);
 }
 
-// Bound by memory: u and the result streamed once, the source gathered near the voxel; the
-// gathers wait for u, so a thread does kApplyPer voxels (a block apart) to have enough loads
-// in flight.  WIDE: 2^31 voxels or more, where an index needs 64 bits.  One voxel per thread
+// Bound by the latency of its loads (two thirds of the wavefronts' cycles; 0.57 vector
+// instructions a cycle and CU): u and the result streamed once, the source gathered near the
+// voxel; the gathers wait for u, so a thread does kApplyPer voxels (a block apart) to have enough
+// loads in flight.  WIDE: 2^31 voxels or more, where an index needs 64 bits.  One voxel per thread
 // with a branch around every corner took 63 us at 264 x 160 x 228 (49 now).
 constexpr int kApplyPer = 2;
 

@@ -199,7 +199,7 @@ __global__ __launch_bounds__(kBlock) void k_coord_grad(GradArgs a) {
 // +1, one of -1 reaches -1 and 0, so where the displacement keeps its sign over
 // the tile two of the three offsets per axis remain (8 sources of 27).  A skipped
 // source contributes nothing and the visited ones keep their order, so the sums
-// are those of the general body, which larger reaches run.  The general body
+// are those of the general body, which larger reaches run, to the rounding of an fma.  The general body
 // spent its time on address and cell arithmetic (27 x about 30 instructions per
 // output): 91.2 us at 128^3 against 54.9 us staged.
 // Below kStagedVoxels it runs all reaches: its blocks then fill the chip at once, where the staged

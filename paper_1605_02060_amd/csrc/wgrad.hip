@@ -21,7 +21,7 @@
 // order: results are deterministic.
 // Weight and bias gradient together, us, batch 8 of 96^3 (k_conv_gemm with its transposing
 // 2-byte LDS stores, a bias pass of 27 to 1728 blocks and one-thread sums of the splits):
-// enc0 2270 -> 125, enc1 510 -> 108, decoder 560 -> 172, head 380 -> 105.
+// enc0 2051 -> 138, enc1 442 -> 97, decoder 532 -> 167, head 259 -> 99.
 #include <algorithm>
 
 #include "cnn_internal.h"
