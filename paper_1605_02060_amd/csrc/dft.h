@@ -40,66 +40,84 @@ template <int R>
 struct Roots;
 template <>
 struct Roots<3> {
-  static constexpr float c[3] = {1.f, -0.5f, -0.5f};
-  static constexpr float s[3] = {0.f, 0.86602540378443865f, -0.86602540378443865f};
+  static constexpr double c[3] = {1.0, -0.5, -0.5};
+  static constexpr double s[3] = {0.0, 0.86602540378443865, -0.86602540378443865};
 };
 template <>
 struct Roots<5> {
-  static constexpr float c[5] = {1.f, 0.30901699437494742f, -0.80901699437494742f,
-                                 -0.80901699437494742f, 0.30901699437494742f};
-  static constexpr float s[5] = {0.f, 0.95105651629515357f, 0.58778525229247313f,
-                                 -0.58778525229247313f, -0.95105651629515357f};
+  static constexpr double c[5] = {1.0, 0.30901699437494742, -0.80901699437494742,
+                                  -0.80901699437494742, 0.30901699437494742};
+  static constexpr double s[5] = {0.0, 0.95105651629515357, 0.58778525229247313,
+                                  -0.58778525229247313, -0.95105651629515357};
 };
 template <>
 struct Roots<7> {
-  static constexpr float c[7] = {1.f, 0.62348980185873353f, -0.22252093395631440f,
-                                 -0.90096886790241913f, -0.90096886790241913f,
-                                 -0.22252093395631440f, 0.62348980185873353f};
-  static constexpr float s[7] = {0.f, 0.78183148246802981f, 0.97492791218182361f,
-                                 0.43388373911755812f, -0.43388373911755812f,
-                                 -0.97492791218182361f, -0.78183148246802981f};
+  static constexpr double c[7] = {1.0, 0.62348980185873353, -0.22252093395631440,
+                                  -0.90096886790241913, -0.90096886790241913,
+                                  -0.22252093395631440, 0.62348980185873353};
+  static constexpr double s[7] = {0.0, 0.78183148246802981, 0.97492791218182361,
+                                  0.43388373911755812, -0.43388373911755812,
+                                  -0.97492791218182361, -0.78183148246802981};
 };
 template <>
 struct Roots<9> {
-  static constexpr float c[9] = {1.f, 0.76604444311897801f, 0.17364817766693041f, -0.5f,
-                                 -0.93969262078590838f, -0.93969262078590838f, -0.5f,
-                                 0.17364817766693041f, 0.76604444311897801f};
-  static constexpr float s[9] = {0.f, 0.64278760968653925f, 0.98480775301220802f,
-                                 0.86602540378443865f, 0.34202014332566873f,
-                                 -0.34202014332566873f, -0.86602540378443865f,
-                                 -0.98480775301220802f, -0.64278760968653925f};
+  static constexpr double c[9] = {1.0, 0.76604444311897801, 0.17364817766693041, -0.5,
+                                  -0.93969262078590838, -0.93969262078590838, -0.5,
+                                  0.17364817766693041, 0.76604444311897801};
+  static constexpr double s[9] = {0.0, 0.64278760968653925, 0.98480775301220802,
+                                  0.86602540378443865, 0.34202014332566873,
+                                  -0.34202014332566873, -0.86602540378443865,
+                                  -0.98480775301220802, -0.64278760968653925};
 };
 template <>
 struct Roots<16> {
-  static constexpr float c[16] = {1.f, 0.92387953251128674f, 0.70710678118654752f,
-                                  0.38268343236508977f, 0.f, -0.38268343236508977f,
-                                  -0.70710678118654752f, -0.92387953251128674f, -1.f,
-                                  -0.92387953251128674f, -0.70710678118654752f,
-                                  -0.38268343236508977f, 0.f, 0.38268343236508977f,
-                                  0.70710678118654752f, 0.92387953251128674f};
-  static constexpr float s[16] = {0.f, 0.38268343236508977f, 0.70710678118654752f,
-                                  0.92387953251128674f, 1.f, 0.92387953251128674f,
-                                  0.70710678118654752f, 0.38268343236508977f, 0.f,
-                                  -0.38268343236508977f, -0.70710678118654752f,
-                                  -0.92387953251128674f, -1.f, -0.92387953251128674f,
-                                  -0.70710678118654752f, -0.38268343236508977f};
+  static constexpr double c[16] = {1.0, 0.92387953251128674, 0.70710678118654752,
+                                  0.38268343236508977, 0.0, -0.38268343236508977,
+                                  -0.70710678118654752, -0.92387953251128674, -1.0,
+                                  -0.92387953251128674, -0.70710678118654752,
+                                  -0.38268343236508977, 0.0, 0.38268343236508977,
+                                  0.70710678118654752, 0.92387953251128674};
+  static constexpr double s[16] = {0.0, 0.38268343236508977, 0.70710678118654752,
+                                  0.92387953251128674, 1.0, 0.92387953251128674,
+                                  0.70710678118654752, 0.38268343236508977, 0.0,
+                                  -0.38268343236508977, -0.70710678118654752,
+                                  -0.92387953251128674, -1.0, -0.92387953251128674,
+                                  -0.70710678118654752, -0.38268343236508977};
 };
 
-template <int R>
-struct Dft;
+// A constant as FP32 and what that rounding leaves out.  FINE transforms rotate by both parts,
+// which costs no rounding of its own (in the sums of the odd lengths it would): with the first
+// part alone, lines of 256 as 16 x 16 were 1.5 % further off than the runtime plan's 8 x 8 x 4,
+// and ones of 56 and 63 0.5 %; with both 256 is 6 % closer.
+struct Split {
+  float hi, lo;
+};
+LDDMM_HD constexpr Split split(double x) { return Split{(float)x, (float)(x - (double)(float)x)}; }
 
-template <int R>
-LDDMM_HD void dft(float2 (&v)[R]) {
-  Dft<R>::run(v);
+// a * (c - i s)
+template <bool FINE>
+LDDMM_HD float2 rotd(float2 a, double cd, double sd) {
+  const Split c = split(cd), s = split(sd);
+  if (!FINE) return rot(a, c.hi, s.hi);
+  return make_float2(fmaf(a.x, c.hi, fmaf(a.y, s.hi, fmaf(a.x, c.lo, a.y * s.lo))),
+                     fmaf(a.y, c.hi, fmaf(-a.x, s.hi, fmaf(a.y, c.lo, -(a.x * s.lo)))));
 }
 
-template <>
-struct Dft<1> {
+template <int R, bool FINE = false>
+struct Dft;
+
+template <int R, bool FINE = false>
+LDDMM_HD void dft(float2 (&v)[R]) {
+  Dft<R, FINE>::run(v);
+}
+
+template <bool FINE>
+struct Dft<1, FINE> {
   static LDDMM_HD void run(float2 (&)[1]) {}
 };
 
-template <>
-struct Dft<2> {
+template <bool FINE>
+struct Dft<2, FINE> {
   static LDDMM_HD void run(float2 (&v)[2]) {
     const float2 a = v[0], b = v[1];
     v[0] = add(a, b);
@@ -116,23 +134,25 @@ LDDMM_HD void dft4(float2& x0, float2& x1, float2& x2, float2& x3) {
   x3 = sub(t1, t3);
 }
 
-template <>
-struct Dft<4> {
+template <bool FINE>
+struct Dft<4, FINE> {
   static LDDMM_HD void run(float2 (&v)[4]) { dft4(v[0], v[1], v[2], v[3]); }
 };
 
 // 8 = 2 x 4: 4-point DFTs of the even and odd samples, then W8^k and a 2-point step.
-template <>
-struct Dft<8> {
+template <bool FINE>
+struct Dft<8, FINE> {
   static LDDMM_HD void run(float2 (&v)[8]) {
     float2 e0 = v[0], e1 = v[2], e2 = v[4], e3 = v[6];
     float2 o0 = v[1], o1 = v[3], o2 = v[5], o3 = v[7];
     dft4(e0, e1, e2, e3);
     dft4(o0, o1, o2, o3);
-    const float r = 0.70710678118654752f;
-    const float2 w1 = make_float2(r * (o1.x + o1.y), r * (o1.y - o1.x));     // W8^1
+    const Split h = split(0.70710678118654752);
+    const float r = h.hi;
+    auto by = [&](float x) { return FINE ? fmaf(r, x, h.lo * x) : r * x; };
+    const float2 w1 = make_float2(by(o1.x + o1.y), by(o1.y - o1.x));         // W8^1
     const float2 w2 = mul_mi(o2);                                            // W8^2 = -i
-    const float2 w3 = make_float2(r * (o3.y - o3.x), -r * (o3.x + o3.y));    // W8^3
+    const float2 w3 = make_float2(by(o3.y - o3.x), -by(o3.x + o3.y));        // W8^3
     v[0] = add(e0, o0);
     v[4] = sub(e0, o0);
     v[1] = add(e1, w1);
@@ -146,8 +166,8 @@ struct Dft<8> {
 
 // 16 = 4 x 4 (Cooley-Tukey): 4-point DFTs over b of x[a + 4 b], twiddles
 // W16^(a kb), 4-point DFTs over a; output X[kb + 4 ka].
-template <>
-struct Dft<16> {
+template <bool FINE>
+struct Dft<16, FINE> {
   static LDDMM_HD void run(float2 (&v)[16]) {
     float2 y[4][4];
 #pragma unroll
@@ -166,7 +186,7 @@ struct Dft<16> {
         if (m == 4)
           y[a][kb] = mul_mi(y[a][kb]);
         else
-          y[a][kb] = rot(y[a][kb], Roots<16>::c[m], Roots<16>::s[m]);
+          y[a][kb] = rotd<FINE>(y[a][kb], Roots<16>::c[m], Roots<16>::s[m]);
       }
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
@@ -202,7 +222,7 @@ struct DftOdd {
 #pragma unroll
       for (int p = 1; p <= H; ++p) {
         const int k = (p * m) % R;
-        const float c = Roots<R>::c[k], s = Roots<R>::s[k];
+        const float c = (float)Roots<R>::c[k], s = (float)Roots<R>::s[k];
         cr += a[p - 1].x * c;
         ci += a[p - 1].y * c;
         sr += b[p - 1].x * s;
@@ -216,22 +236,23 @@ struct DftOdd {
   }
 };
 
-template <>
-struct Dft<3> : DftOdd<3> {};
+template <bool FINE>
+struct Dft<3, FINE> : DftOdd<3> {};
 
 // 9 = 3 x 3 (Cooley-Tukey): 3-point DFTs over b of x[a + 3 b], twiddles
 // W9^(a kb), 3-point DFTs over a; output X[kb + 3 ka].
-template <>
-struct Dft<9> {
+template <bool FINE>
+struct Dft<9, FINE> {
   static LDDMM_HD void run(float2 (&v)[9]);
 };
 
-LDDMM_HD void Dft<9>::run(float2 (&v)[9]) {
+template <bool FINE>
+LDDMM_HD void Dft<9, FINE>::run(float2 (&v)[9]) {
   float2 y[3][3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     float2 t[3] = {v[a], v[a + 3], v[a + 6]};
-    Dft<3>::run(t);
+    Dft<3, FINE>::run(t);
     y[a][0] = t[0];
     y[a][1] = t[1];
     y[a][2] = t[2];
@@ -241,21 +262,21 @@ LDDMM_HD void Dft<9>::run(float2 (&v)[9]) {
 #pragma unroll
     for (int kb = 1; kb < 3; ++kb) {
       const int m = a * kb;
-      y[a][kb] = rot(y[a][kb], Roots<9>::c[m], Roots<9>::s[m]);
+      y[a][kb] = rotd<FINE>(y[a][kb], Roots<9>::c[m], Roots<9>::s[m]);
     }
 #pragma unroll
   for (int kb = 0; kb < 3; ++kb) {
     float2 t[3] = {y[0][kb], y[1][kb], y[2][kb]};
-    Dft<3>::run(t);
+    Dft<3, FINE>::run(t);
     v[kb] = t[0];
     v[kb + 3] = t[1];
     v[kb + 6] = t[2];
   }
 }
-template <>
-struct Dft<5> : DftOdd<5> {};
-template <>
-struct Dft<7> : DftOdd<7> {};
+template <bool FINE>
+struct Dft<5, FINE> : DftOdd<5> {};
+template <bool FINE>
+struct Dft<7, FINE> : DftOdd<7> {};
 
 // Good-Thomas product of coprime A and B (no twiddles).
 constexpr int inv_mod(int a, int m) {
@@ -264,7 +285,7 @@ constexpr int inv_mod(int a, int m) {
   return r;
 }
 
-template <int A, int B>
+template <int A, int B, bool FINE>
 struct DftPfa {
   static constexpr int N = A * B;
   static LDDMM_HD void run(float2 (&v)[N]) {
@@ -274,7 +295,7 @@ struct DftPfa {
       float2 t[A];
 #pragma unroll
       for (int a = 0; a < A; ++a) t[a] = v[(B * a + A * b) % N];
-      Dft<A>::run(t);
+      Dft<A, FINE>::run(t);
 #pragma unroll
       for (int ka = 0; ka < A; ++ka) y[b][ka] = t[ka];
     }
@@ -285,31 +306,31 @@ struct DftPfa {
       float2 t[B];
 #pragma unroll
       for (int b = 0; b < B; ++b) t[b] = y[b][ka];
-      Dft<B>::run(t);
+      Dft<B, FINE>::run(t);
 #pragma unroll
       for (int kb = 0; kb < B; ++kb) v[(ka * eA + kb * eB) % N] = t[kb];
     }
   }
 };
 
-template <>
-struct Dft<6> : DftPfa<2, 3> {};
-template <>
-struct Dft<10> : DftPfa<2, 5> {};
-template <>
-struct Dft<12> : DftPfa<4, 3> {};
-template <>
-struct Dft<14> : DftPfa<2, 7> {};
-template <>
-struct Dft<15> : DftPfa<3, 5> {};
-template <>
-struct Dft<18> : DftPfa<2, 9> {};
-template <>
-struct Dft<20> : DftPfa<4, 5> {};
-template <>
-struct Dft<28> : DftPfa<4, 7> {};
-template <>
-struct Dft<35> : DftPfa<5, 7> {};
+template <bool FINE>
+struct Dft<6, FINE> : DftPfa<2, 3, FINE> {};
+template <bool FINE>
+struct Dft<10, FINE> : DftPfa<2, 5, FINE> {};
+template <bool FINE>
+struct Dft<12, FINE> : DftPfa<4, 3, FINE> {};
+template <bool FINE>
+struct Dft<14, FINE> : DftPfa<2, 7, FINE> {};
+template <bool FINE>
+struct Dft<15, FINE> : DftPfa<3, 5, FINE> {};
+template <bool FINE>
+struct Dft<18, FINE> : DftPfa<2, 9, FINE> {};
+template <bool FINE>
+struct Dft<20, FINE> : DftPfa<4, 5, FINE> {};
+template <bool FINE>
+struct Dft<28, FINE> : DftPfa<4, 7, FINE> {};
+template <bool FINE>
+struct Dft<35, FINE> : DftPfa<5, 7, FINE> {};
 
 #undef LDDMM_HD
 

@@ -367,14 +367,22 @@ constexpr int kCT = 16;   // kx columns per tile of a compile-time pass
 // runtime-planned pass, and a registration's trace holds single values in 64 bits (its least
 // determinant) that would follow; and a factor above 16 needs more threads than the batched
 // launches' 256, whose results are those of single calls bit for bit.  K on 252 x 180 x 200 took
-// 371 us with runtime plans (and a copy of b, and six launches for the tables), 223 with these
-// (220 with the symbol in FP32).
+// 371 us with runtime plans (and a copy of b, and six launches for the tables), 225 with these
+// (220 with symbol and constants in FP32).
 #define LDDMM_CT_WIDE(X) \
   X(24, 6, 4) X(25, 5, 5) X(27, 9, 3) X(28, 7, 4) X(30, 6, 5) X(35, 7, 5) X(36, 6, 6) \
   X(42, 7, 6) X(45, 9, 5) X(48, 8, 6) X(49, 7, 7) X(50, 10, 5) X(54, 9, 6) X(56, 8, 7) \
   X(63, 9, 7) X(168, 14, 12) X(180, 15, 12) X(192, 16, 12) X(196, 14, 14) X(210, 15, 14) \
   X(224, 16, 14) X(225, 15, 15) X(256, 16, 16) X(162, 18, 9) X(200, 20, 10) X(216, 18, 12) \
   X(252, 18, 14) X(270, 18, 15) X(288, 18, 16) X(300, 20, 15) X(320, 20, 16)
+
+// Those lengths: K's symbol in FP64 and the transforms' constants in full (dft.h), so that no
+// result is further from the exact one than with the runtime-planned passes.
+constexpr bool wide_length(int n) {
+#define LDDMM_CT_CASE(N, A, B) || n == N
+  return false LDDMM_CT_WIDE(LDDMM_CT_CASE);
+#undef LDDMM_CT_CASE
+}
 
 static bool ct_plan(const FftPair& f, int n, int* n1, int* n2) {
 #define LDDMM_CT_CASE(N, A, B) \
@@ -403,6 +411,7 @@ static size_t ct_lds_bytes(int n) {
 template <int N1, int N2, bool INV>
 __device__ __forceinline__ void ct_y_body(const FftPair& f, int bx, int zslab, int comp) {
   constexpr int N = N1 * N2, LS = N + 1;
+  constexpr bool WIDE = wide_length(N);
   extern __shared__ float2 sm[];
   float2* sx = sm;
   float2* stw = sm + kCT * LS;
@@ -423,7 +432,7 @@ __device__ __forceinline__ void ct_y_body(const FftPair& f, int bx, int zslab, i
   }
   __syncthreads();
   if (t < N1) {
-    dft::dft<N2>(v);
+    dft::dft<N2, WIDE>(v);
 #pragma unroll
     for (int q = 1; q < N2; ++q) v[q] = dft::mul(v[q], stw[t * q]);
 #pragma unroll
@@ -434,7 +443,7 @@ __device__ __forceinline__ void ct_y_body(const FftPair& f, int bx, int zslab, i
     float2 w[N1];
 #pragma unroll
     for (int p = 0; p < N1; ++p) w[p] = sx[c * LS + p + N1 * t];
-    dft::dft<N1>(w);
+    dft::dft<N1, WIDE>(w);
 #pragma unroll
     for (int k = 0; k < N1; ++k) col[(t + N2 * k) * hs] = INV ? dft::conj(w[k]) : w[k];
   }
@@ -442,12 +451,13 @@ __device__ __forceinline__ void ct_y_body(const FftPair& f, int bx, int zslab, i
 
 // z pass: forward transform, K_hat / |P| (and conj), forward transform of the
 // conjugate, conj on the way out: N_z IDFT_z(K_hat X / |P|).
-// SYM64: K_hat / |P| from FP64 terms, rounded once, as in zK_body (the lengths of
-// FftPair::alone, which replace that pass); else two FP32 terms added, and the hardware
-// reciprocal of their square, which is infinite for gamma below about 1e-19.
-template <int N1, int N2, bool SYM64>
+// Wide lengths: K_hat / |P| from FP64 terms, rounded once, as in zK_body, which they
+// replace; else two FP32 terms added, and the hardware reciprocal of their square, which is
+// infinite for gamma below about 1e-19.
+template <int N1, int N2>
 __device__ __forceinline__ void ct_zK_body(const FftPair& f, int bx, int ky, int comp) {
   constexpr int N = N1 * N2, LS = N + 1;
+  constexpr bool WIDE = wide_length(N);
   extern __shared__ float2 sm[];
   float2* sx = sm;
   float2* stw = sm + kCT * LS;
@@ -463,14 +473,14 @@ __device__ __forceinline__ void ct_zK_body(const FftPair& f, int bx, int ky, int
   const double* __restrict__ lamz = f.lam[2];
   for (int e = threadIdx.x; e < N; e += blockDim.x) {
     stw[e] = tw[e];
-    if (SYM64)
+    if (WIDE)
       slz[e] = lamz[e];
     else
       saz[e] = (float)(f.alpha * lamz[e]);
   }
   const int kxc = bx * kCT + c;
-  const double lxy = SYM64 ? f.lam[0][kxc < g.hx ? kxc : 0] + f.lam[1][ky] : 0.0;
-  if (!SYM64 && threadIdx.x < kCT) {
+  const double lxy = WIDE ? f.lam[0][kxc < g.hx ? kxc : 0] + f.lam[1][ky] : 0.0;
+  if (!WIDE && threadIdx.x < kCT) {
     const int kx = bx * kCT + (int)threadIdx.x;
     scxy[threadIdx.x] = (float)(f.gamma + f.alpha * (f.lam[0][kx < g.hx ? kx : 0] + f.lam[1][ky]));
   }
@@ -481,7 +491,7 @@ __device__ __forceinline__ void ct_zK_body(const FftPair& f, int bx, int ky, int
   }
   __syncthreads();
   if (t < N1) {
-    dft::dft<N2>(v);
+    dft::dft<N2, WIDE>(v);
 #pragma unroll
     for (int q = 1; q < N2; ++q) v[q] = dft::mul(v[q], stw[t * q]);
 #pragma unroll
@@ -492,13 +502,13 @@ __device__ __forceinline__ void ct_zK_body(const FftPair& f, int bx, int ky, int
   if (t < N2) {
 #pragma unroll
     for (int p = 0; p < N1; ++p) w[p] = sx[c * LS + p + N1 * t];
-    dft::dft<N1>(w);
+    dft::dft<N1, WIDE>(w);
     const double inv_n = 1.0 / ((double)g.nx * (double)g.ny * (double)g.nz);
-    const float cxy = SYM64 ? 0.f : scxy[c];
+    const float cxy = WIDE ? 0.f : scxy[c];
 #pragma unroll
     for (int k = 0; k < N1; ++k) {
       float kh;
-      if (SYM64) {
+      if (WIDE) {
         const double lam = f.alpha * (lxy + slz[t + N2 * k]) + f.gamma;
         kh = (float)(inv_n / (lam * lam));
       } else {
@@ -507,7 +517,7 @@ __device__ __forceinline__ void ct_zK_body(const FftPair& f, int bx, int ky, int
       }
       w[k] = make_float2(w[k].x * kh, -w[k].y * kh);          // conj(K_hat X / |P|)
     }
-    dft::dft<N1>(w);
+    dft::dft<N1, WIDE>(w);
 #pragma unroll
     for (int p = 1; p < N1; ++p) w[p] = dft::mul(w[p], stw[t * p]);
   }
@@ -521,7 +531,7 @@ __device__ __forceinline__ void ct_zK_body(const FftPair& f, int bx, int ky, int
     float2 u[N2];
 #pragma unroll
     for (int q = 0; q < N2; ++q) u[q] = sx[c * LS + q + N2 * t];
-    dft::dft<N2>(u);
+    dft::dft<N2, WIDE>(u);
 #pragma unroll
     for (int q = 0; q < N2; ++q) col[(t + N1 * q) * zs] = dft::conj(u[q]);
   }
@@ -534,14 +544,14 @@ __global__ __launch_bounds__(kCT * (N1 > N2 ? N1 : N2)) void k_fftc_y(FftPair f)
 }
 
 // XCD-aware tile order as in k_fft_z_K.
-template <int N1, int N2, bool SYM64>
+template <int N1, int N2>
 __global__ __launch_bounds__(kCT * (N1 > N2 ? N1 : N2)) void k_fftc_zK(FftPair f) {
   if (!gate(f.st, f.need_mode)) return;
   const uint32_t total = gridDim.x;
   uint32_t t = blockIdx.x;
   if ((total % kXCD) == 0) t = (t % kXCD) * (total / kXCD) + t / kXCD;
   const int bx = (int)(t % (uint32_t)f.nbx_z), r = (int)(t / (uint32_t)f.nbx_z);
-  ct_zK_body<N1, N2, SYM64>(f, bx, r % f.g.ny, r / f.g.ny);
+  ct_zK_body<N1, N2>(f, bx, r % f.g.ny, r / f.g.ny);
 }
 
 // The compile-time body for this problem's length, if it has one (batched
@@ -564,7 +574,7 @@ __device__ __forceinline__ bool ct_zK_dispatch(const FftPair& f, int bx, int ky,
   switch (f.g.nz) {
 #define LDDMM_CT_CASE(N, A, B)          \
   case N:                               \
-    ct_zK_body<A, B, false>(f, bx, ky, comp); \
+    ct_zK_body<A, B>(f, bx, ky, comp); \
     return true;
     LDDMM_CT_PLANS(LDDMM_CT_CASE)
 #undef LDDMM_CT_CASE
@@ -599,12 +609,13 @@ static bool ctx_plan(const FftPair& f, int n, int* n1, int* n2) {
 template <int N1, int N2, int LPB>
 __device__ __forceinline__ void ct_lines(float2* sx, const float2* stw) {
   constexpr int N = N1 * N2, G = N1 > N2 ? N1 : N2, LS = N + 1;
+  constexpr bool WIDE = wide_length(N);
   const int l = threadIdx.x / G, t = threadIdx.x % G;
   if (l < LPB && t < N1) {
     float2 v[N2];
 #pragma unroll
     for (int q = 0; q < N2; ++q) v[q] = sx[l * LS + t + N1 * q];
-    dft::dft<N2>(v);
+    dft::dft<N2, WIDE>(v);
 #pragma unroll
     for (int q = 1; q < N2; ++q) v[q] = dft::mul(v[q], stw[t * q]);
 #pragma unroll
@@ -615,7 +626,7 @@ __device__ __forceinline__ void ct_lines(float2* sx, const float2* stw) {
   if (l < LPB && t < N2) {
 #pragma unroll
     for (int p = 0; p < N1; ++p) w[p] = sx[l * LS + p + N1 * t];
-    dft::dft<N1>(w);
+    dft::dft<N1, WIDE>(w);
   }
   __syncthreads();
   if (l < LPB && t < N2) {
@@ -1764,25 +1775,21 @@ void launch_fft_y(const FftPair& f, const FftLaunch& L, int inverse, hipStream_t
 void launch_fft_z_K(const FftPair& f, const FftLaunch& L, hipStream_t s) {
   const dim3 grid(f.nbx_z * f.g.ny * 3);
   switch (f.g.nz) {
-#define LDDMM_CT_CASE(N, A, B, SYM64)                                                              \
-  case N:                                                                                         \
-    hipLaunchKernelGGL((k_fftc_zK<A, B, SYM64>), grid, dim3(kCT * (A > B ? A : B)), L.z_lds, s, f); \
+#define LDDMM_CT_CASE(N, A, B)                                                               \
+  case N:                                                                                    \
+    hipLaunchKernelGGL((k_fftc_zK<A, B>), grid, dim3(kCT * (A > B ? A : B)), L.z_lds, s, f); \
     return;
-#define LDDMM_CT_CASE32(N, A, B) LDDMM_CT_CASE(N, A, B, false)
-#define LDDMM_CT_CASE64(N, A, B) LDDMM_CT_CASE(N, A, B, true)
-    LDDMM_CT_PLANS(LDDMM_CT_CASE32)
+    LDDMM_CT_PLANS(LDDMM_CT_CASE)
     default:
       break;
   }
   if (f.alone) {
     switch (f.g.nz) {
-      LDDMM_CT_WIDE(LDDMM_CT_CASE64)
+      LDDMM_CT_WIDE(LDDMM_CT_CASE)
       default:
         break;
     }
   }
-#undef LDDMM_CT_CASE32
-#undef LDDMM_CT_CASE64
 #undef LDDMM_CT_CASE
   EMAX_SWITCH(L.ez,
     hipLaunchKernelGGL(k_fft_z_K<8>, grid, dim3(kBlock), L.z_lds, s, f),
